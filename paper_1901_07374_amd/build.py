@@ -18,6 +18,9 @@ FLAGS = [
     "-ffp-contract=off",
     # packed FP32 instructions stay off in all device code
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    # constants (the 64-bit literals of exp and log) are formed where they are
+    # used: hoisted out of loops they spill registers
+    "-mllvm", "-disable-machine-licm",
     "-Wno-unused-command-line-argument",
     "-I", os.path.join(ROOT, "include"),
 ]

@@ -41,7 +41,7 @@ struct Layout {
     size_t GQ, GH, U0, U1, VW, sig, eps_p, eps_rate, d_init, w_p, f_void, e, D, force, fvisc, hs, err,
         arad, ccnt, ccol, ubuild, cbox, hslot, hboff, gpos, gref,
         spec_off, bbox, keys, vals, bc_list, bc_ptr, diag_seg, diag_part, backup,
-        run, done, tile_list, run_count, halo_a, halo_cnt_a, lcol_a, tile_list_a;
+        run, done, tile_list, run_count, halo_a, halo_cnt_a, lcol_a, tile_list_a, pslot;
     int64_t diag_chunk_cap;
     size_t state_begin, backup_bytes;
     size_t total;
@@ -97,8 +97,8 @@ Layout make_layout(int64_t n, int32_t n_spec, int32_t n_bc, int32_t k_cap, bool 
     L.t = take((size_t)n_spec * 8);
     // evolving state, contiguous (saved and restored by the autotuner)
     L.state_begin = align_up(cur);
-    L.GQ = take(np * (mixed ? sizeof(GQRec<float>) : sizeof(GQRec<double>)));
-    L.GH = take(np * (mixed ? sizeof(GHRec<float>) : sizeof(GHRec<double>)));
+    L.GQ = take(np * (mixed ? sizeof(GQRec<float>) : sizeof(GQRec<double>)) + kRecPad);
+    L.GH = take(np * (mixed ? sizeof(GHRec<float>) : sizeof(GHRec<double>)) + kRecPad);
     L.U0 = take(np * sizeof(D4));
     L.U1 = take(np * sizeof(D4));
     L.VW = take(np * sizeof(D4));
@@ -138,6 +138,7 @@ Layout make_layout(int64_t n, int32_t n_spec, int32_t n_bc, int32_t k_cap, bool 
     L.halo_cnt_a = take((size_t)L.n_tiles * 4);
     L.lcol_a = take((size_t)k_cap * np * 2);
     L.tile_list_a = take((size_t)L.n_tiles * 4);
+    L.pslot = take(np * kPackWords * 4);
     L.total = align_up(cur);
     return L;
 }
@@ -166,6 +167,8 @@ struct tlsph_ctx {
     bool staged_ok = false;     // the staged force pass fits this device's LDS
     size_t lds_b = 0;           // its dynamic LDS bytes
     int max_lds = 0;            // LDS bytes a workgroup may use on this device
+    int n_cu = 1;               // its compute units
+    int max_nnb = 0;            // most neighbours of a particle
     int tile_auto = kTile;      // tile size chosen at build
     std::string last_error;
     // per-kernel timing (every timing_stride-th step while enabled)
@@ -241,6 +244,7 @@ void wire_state(tlsph_ctx* c) {
     s.halo_a = s.halo;
     s.halo_cnt_a = s.halo_cnt;
     s.lcol_a = s.lcol;
+    s.pslot = at<uint32_t>(c, L.pslot);
     s.staged = 0;
     s.lds_slots = 0;
     s.Linv = at<double>(c, L.Linv);
@@ -430,7 +434,7 @@ static_assert(kHaloPad >= 2 * (2 * kTile) && kHaloPad >= 4 * kTile,
 // given arrays; their largest halo, or -1 where the lists cannot be built
 // (the sort's LDS, or staging switched off).  Synchronises.
 tlsph_status build_tile_lists(tlsph_ctx* c, int T, size_t halo, size_t halo_cnt, size_t lcol,
-                              int* largest, hipStream_t stream) {
+                              uint32_t* pslot, int* largest, hipStream_t stream) {
     const Layout& L = c->L;
     *largest = -1;
     int E = 256;
@@ -440,11 +444,55 @@ tlsph_status build_tile_lists(tlsph_ctx* c, int T, size_t halo, size_t halo_cnt,
     const int32_t zero = 0;
     HIPCHK(c, hipMemcpyAsync(c->ws + L.err + 16, &zero, 4, hipMemcpyHostToDevice, stream));
     HIPCHK(c, launch_halo(c->st, L.k_cap, T, at<int32_t>(c, halo), at<int32_t>(c, halo_cnt),
-                          at<uint16_t>(c, lcol), stream));
+                          at<uint16_t>(c, lcol), pslot, stream));
     int32_t lg = 0;
     HIPCHK(c, hipMemcpyAsync(&lg, c->ws + L.err + 16, 4, hipMemcpyDeviceToHost, stream));
     HIPCHK(c, hipStreamSynchronize(stream));
     *largest = lg;
+    return TLSPH_OK;
+}
+
+// The form of the staged force pass at the current tiles with `sub` lanes per
+// particle; every form gives the same bits.  Measured on whole passes:
+// - pipelined over as many workgroups as fit (two lanes, one support for all,
+//   every particle's pairs within its registers, the image in LDS) where a CU
+//   then works on at least 160 particles at a time (FP64, 4.1M particles:
+//   tiles of 256 631 us, of 128, one to a CU, 851 against 757 in two sweeps) and
+//   the walk is long enough for its uneven end: four tiles a workgroup (200k
+//   FP64, tiles of 196: 39.8 us, 48.4 in two sweeps), eight in the mixed form
+//   (4.1M: 511 us, 607 in one sweep; 200k, three or four tiles: 30.9, 29.0).
+// - FP64, two sweeps where their smaller image lets more workgroups share a CU
+//   and the tiles need the room (395k particles, tiles of 97, three instead of
+//   two: 99.8 us, 118 in one sweep).
+// - else one sweep: one barrier instead of three (25k particles FP64, every
+//   tile resident at once: 12.6 us, 13.3 in two sweeps).
+tlsph_status set_form_b(tlsph_ctx* c, int sub) {
+    const Layout& L = c->L;
+    const bool var_h = c->st.var_h != 0;
+    const size_t slots = (size_t)c->st.lds_slots, lds = (size_t)c->max_lds;
+    const size_t one = slots * staged_one_bytes(L.mixed, var_h);
+    const size_t two = slots * staged_sweep_bytes(var_h);
+    const size_t pipe = slots * staged_pipe_bytes(L.mixed);
+    const int64_t tiles = (L.n + c->st.tile - 1) / c->st.tile;
+    c->st.grid_b = (int32_t)tiles;
+    c->st.form_b = kFormOne;
+    c->lds_b = one;
+    if (!L.mixed && lds / two > lds / one && tiles > (int64_t)(lds / one) * c->n_cu) {
+        c->st.form_b = kFormSweeps;
+        c->lds_b = two;
+    }
+    if (sub == 2 && !var_h && c->max_nnb <= staged_pipe_neighbours() && pipe <= lds) {
+        int per_cu = 0;
+        HIPCHK(c, prepare_staged(pipe));
+        HIPCHK(c, staged_blocks_per_cu(L.mixed, c->st.tile * sub, pipe, &per_cu));
+        const int64_t room = (int64_t)c->n_cu * per_cu;
+        if (per_cu * c->st.tile >= 160 && 2 * tiles > (L.mixed ? 15 : 7) * room) {
+            c->st.form_b = kFormPipe;
+            c->lds_b = pipe;
+            c->st.grid_b = (int32_t)room;
+        }
+    }
+    HIPCHK(c, prepare_staged(c->lds_b));
     return TLSPH_OK;
 }
 
@@ -467,15 +515,16 @@ tlsph_status set_tile_lists(tlsph_ctx* c, int T, hipStream_t stream) {
     c->st.halo_cap = T * L.k_cap;
     if (!c->a_own) c->st.tile_a = T;
     int largest = -1;
-    tlsph_status bs = build_tile_lists(c, T, L.halo, L.halo_cnt, L.lcol, &largest, stream);
+    tlsph_status bs = build_tile_lists(c, T, L.halo, L.halo_cnt, L.lcol,
+                                       at<uint32_t>(c, L.pslot), &largest, stream);
     if (bs != TLSPH_OK || largest < 0) return bs;
     c->largest_b = largest;
-    const size_t lds = (size_t)(T + largest) * staged_record_bytes(L.mixed, c->st.var_h != 0);
+    const size_t lds = (size_t)(T + largest) * staged_one_bytes(L.mixed, c->st.var_h != 0);
     if (lds <= (size_t)c->max_lds && T + largest <= 65536) {
-        HIPCHK(c, prepare_staged(lds));
         c->staged_ok = true;
-        c->lds_b = lds;
         c->st.lds_slots = T + largest;
+        tlsph_status fs = set_form_b(c, c->sub_b);
+        if (fs != TLSPH_OK) return fs;
         if (!c->a_own) set_pass_a_shape(c, T, largest);
     }
     return TLSPH_OK;
@@ -503,7 +552,7 @@ tlsph_status set_tile_a_lists(tlsph_ctx* c, int T, hipStream_t stream) {
     c->st.lcol_a = at<uint16_t>(c, L.lcol_a);
     c->st.tile_a = T;
     int largest = -1;
-    tlsph_status bs = build_tile_lists(c, T, L.halo_a, L.halo_cnt_a, L.lcol_a, &largest, stream);
+    tlsph_status bs = build_tile_lists(c, T, L.halo_a, L.halo_cnt_a, L.lcol_a, nullptr, &largest, stream);
     if (bs != TLSPH_OK) return bs;
     if (largest >= 0) set_pass_a_shape(c, T, largest);
     return TLSPH_OK;
@@ -751,6 +800,8 @@ tlsph_status tlsph_build_neighbors(tlsph_ctx* c, const double* X, const double* 
     int n_cu = 0;
     HIPCHK(c, hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev));
     if (n_cu < 1) n_cu = 1;
+    c->n_cu = n_cu;
+    c->max_nnb = err[1];
     {
         const int64_t per_round = (int64_t)kTile * n_cu;
         const int64_t rounds = (L.n + per_round - 1) / per_round;
@@ -1119,32 +1170,41 @@ static tlsph_status autotune_all(tlsph_ctx* c, hipStream_t stream) {
     hipEvent_t e0, e1;
     HIPCHK(c, hipEventCreate(&e0));
     HIPCHK(c, hipEventCreate(&e1));
-    const int reps = 10;   // launches timed per candidate (their spread is about 2 %)
-    auto timed = [&](auto&& launch, float* ms) -> tlsph_status {
+    // launches timed per candidate (their spread is about 2 %); one that takes
+    // 1.3 times the best so far over its first two is not timed further
+    const int reps = 10, first_reps = 2;
+    auto timed = [&](auto&& launch, float best, float* ms) -> tlsph_status {
         // every candidate starts from the saved state
         HIPCHK(c, hipMemcpyAsync(state, backup, L.backup_bytes, hipMemcpyDeviceToDevice, stream));
-        hipError_t e = hipSuccess;
-        for (int r = 0; r < reps + 1 && e == hipSuccess; ++r) {
-            if (r == 1) HIPCHK(c, hipEventRecord(e0, stream));
-            e = launch();
+        hipError_t e = launch();
+        for (int n : {first_reps, reps}) {
+            HIPCHK(c, hipEventRecord(e0, stream));
+            for (int r = 0; r < n && e == hipSuccess; ++r) e = launch();
+            if (e != hipSuccess) return hip_fail(c, e, "autotune launch");
+            HIPCHK(c, hipEventRecord(e1, stream));
+            HIPCHK(c, hipEventSynchronize(e1));
+            HIPCHK(c, hipEventElapsedTime(ms, e0, e1));
+            *ms /= (float)n;
+            if (*ms > 1.3f * best) return TLSPH_OK;
         }
-        if (e != hipSuccess) return hip_fail(c, e, "autotune launch");
-        HIPCHK(c, hipEventRecord(e1, stream));
-        HIPCHK(c, hipEventSynchronize(e1));
-        HIPCHK(c, hipEventElapsedTime(ms, e0, e1));
         return TLSPH_OK;
     };
     // The two passes are timed separately: unstaged candidates do not depend
     // on the tile size, staged ones are timed per tile size.
-    auto time_b = [&](int staged, int sub, int block, float* ms) -> tlsph_status {
+    auto time_b = [&](int staged, int sub, int block, float best, float* ms) -> tlsph_status {
         c->st.staged = staged;
         const int blk = staged ? c->st.tile * sub : block;
+        if (staged) {
+            tlsph_status fs = set_form_b(c, sub);
+            if (fs != TLSPH_OK) return fs;
+        }
         return timed([&] {
             return launch_pass_b(c->st, c->parity, blk, sub, L.mixed, stream, c->lds_b);
-        }, ms);
+        }, best, ms);
     };
-    auto time_a = [&](int block, float* ms) -> tlsph_status {
-        return timed([&] { return launch_pass_a(c->st, c->parity, block, L.mixed, stream); }, ms);
+    auto time_a = [&](int block, float best, float* ms) -> tlsph_status {
+        return timed([&] { return launch_pass_a(c->st, c->parity, block, L.mixed, stream); },
+                     best, ms);
     };
     // Each pass's fastest shape, chosen on its own: the force pass unstaged
     // (lanes, block) or staged (tile size, lanes); the deformation pass
@@ -1159,23 +1219,24 @@ static tlsph_status autotune_all(tlsph_ctx* c, hipStream_t stream) {
     int bu_sub = 2, bu_blk = 256, au_blk = 256;
     for (const Cand& k : cand_u) {
         float t = 0.0f;
-        tlsph_status st = time_b(0, k.sub, k.block, &t);
+        tlsph_status st = time_b(0, k.sub, k.block, bu, &t);
         if (st != TLSPH_OK) return st;
         if (t < bu) { bu = t; bu_sub = k.sub; bu_blk = k.block; }
     }
     for (int blk : cand_a) {
         float t = 0.0f;
-        tlsph_status st = time_a(blk, &t);
+        tlsph_status st = time_a(blk, au, &t);
         if (st != TLSPH_OK) return st;
         if (t < au) { au = t; au_blk = blk; }
     }
     float bs_best = 1e30f, as_best = 1e30f;
     int bs_sub = 2, bs_tile = 0, as_tile = 0;
     if (!(c->flags & TLSPH_NO_STAGING)) {
-        // Tile sizes: the build's, six fixed ones, and for each of those
-        // the sizes that fill whole rounds at the number of workgroups per
-        // CU the force pass's LDS image allows (the next smaller, and a few
-        // percent larger if that drops a barely started last round).
+        // Tile sizes: the build's, eight fixed ones (the two largest serve the
+        // pipelined force pass), and for each of those the sizes that fill
+        // whole rounds at the number of workgroups per CU the two-lane force
+        // pass's LDS image allows (the next smaller, and a few percent larger
+        // if that drops a barely started last round).
         int dev = 0, lds_cu = 0, n_cu = 0;
         HIPCHK(c, hipGetDevice(&dev));
         HIPCHK(c, hipDeviceGetAttribute(&lds_cu, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor,
@@ -1183,7 +1244,7 @@ static tlsph_status autotune_all(tlsph_ctx* c, hipStream_t stream) {
         HIPCHK(c, hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev));
         if (lds_cu < c->max_lds) lds_cu = c->max_lds;
         if (n_cu < 1) n_cu = 1;
-        std::vector<int> tiles = {c->tile_auto, 128, 112, 96, 88, 80, 64};
+        std::vector<int> tiles = {c->tile_auto, 224, 192, 128, 112, 96, 88, 80, 64};
         const size_t n_fixed = tiles.size();
         for (size_t q = 0; q < tiles.size(); ++q) {
             bool seen = false;
@@ -1192,16 +1253,16 @@ static tlsph_status autotune_all(tlsph_ctx* c, hipStream_t stream) {
             tlsph_status ts = set_tile(c, tiles[q], stream);
             if (ts != TLSPH_OK) return ts;
             if (!c->staged_ok) continue;
-            for (int sub : {4, 2, 1}) {
+            for (int sub : {4, 1, 2}) {   // two lanes last: lds_b below is theirs
                 if (tiles[q] > staged_tile_max(sub)) continue;
                 float t = 0.0f;
-                tlsph_status st = time_b(1, sub, 0, &t);
+                tlsph_status st = time_b(1, sub, 0, bs_best, &t);
                 if (st != TLSPH_OK) return st;
                 if (t < bs_best) { bs_best = t; bs_sub = sub; bs_tile = tiles[q]; }
             }
             if (c->st.staged_lds_a) {
                 float t = 0.0f;
-                tlsph_status st = time_a(0, &t);
+                tlsph_status st = time_a(0, as_best, &t);
                 if (st != TLSPH_OK) return st;
                 if (t < as_best) { as_best = t; as_tile = tiles[q]; }
             }
@@ -1233,6 +1294,10 @@ static tlsph_status autotune_all(tlsph_ctx* c, hipStream_t stream) {
         c->st.staged = b_staged && ok_b;
         c->sub_b = b_staged && ok_b ? bs_sub : bu_sub;
         c->block_b = c->st.staged ? c->st.tile * c->sub_b : bu_blk;
+        if (c->st.staged) {
+            ts = set_form_b(c, c->sub_b);
+            if (ts != TLSPH_OK) return ts;
+        }
         c->block_a = au_blk;
         if (a_staged) {
             ts = set_tile_a(c, as_tile, stream);
@@ -1319,6 +1384,10 @@ tlsph_status tlsph_set_launch_shape(tlsph_ctx* c, const int32_t shape[5], hipStr
         if (ts != TLSPH_OK) return ts;
         if (!c->st.staged_lds_a)
             return fail(c, TLSPH_E_UNSUPPORTED, "the staged deformation pass does not fit LDS");
+    }
+    if (staged) {
+        tlsph_status fs = set_form_b(c, sub);
+        if (fs != TLSPH_OK) return fs;
     }
     c->st.staged = staged;
     c->sub_b = sub;

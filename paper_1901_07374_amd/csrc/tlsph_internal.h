@@ -10,6 +10,12 @@ constexpr int kSlice = 64;          // particles per slice of the sliced neighbo
 constexpr int kCellBits = 14;     // cells per axis < 2^14
 constexpr int kSpecShift = 3 * kCellBits;
 constexpr int kSub = 4;            // partial sums per particle in the force pass (canonical order)
+// A particle's first neighbours as local slots in one record of 16-bit entries:
+// kPackGroups groups of kSub (a bulk particle of a cubic lattice with h = 1.5
+// dx has 18 neighbours), list by list (neighbours t, t + kSub, ... for t < kSub).
+constexpr int kPackGroups = 6;
+constexpr int kPackWords = kPackGroups * kSub / 2;
+constexpr int kPipeGroups = 5;     // groups the pipelined force pass holds in registers
 constexpr int kNDiag = 8;          // doubles per diagnostics record
 constexpr int kDiagChunk = 2048;   // particles per partial sum of the diagnostics
 constexpr int kTile = 256;         // most particles per workgroup tile of the LDS-staged pass
@@ -93,9 +99,12 @@ struct alignas(16) D4 {
 };
 
 // What the force pass gathers from a neighbour besides geometry, in two
-// records so that the deformation pass reads only H: Q = P L^-T with 1 - D,
-// and H = F - I.  R is the storage precision (double, or float in the mixed
-// form); each record is 10 values, aligned to two.
+// records so that its two sweeps (and the deformation pass) each read one: Q =
+// P L^-T with 1 - D, and H = F - I with V0 (1 - D).  R is the storage
+// precision (double, or float in the mixed form); each record is 10 values,
+// aligned to two.  In LDS a record takes an odd number of 16-byte units (5, or
+// 3 whose last half belongs to the record after it: kRecPad bytes follow the
+// last one).
 template <typename R>
 struct alignas(2 * sizeof(R)) GQRec {
     R q[9];
@@ -104,8 +113,13 @@ struct alignas(2 * sizeof(R)) GQRec {
 template <typename R>
 struct alignas(2 * sizeof(R)) GHRec {
     R h[9];
-    R pad;
+    R vw;
 };
+constexpr size_t kRecPad = 8;
+
+// Forms of the staged force pass: one sweep over whole records, two sweeps whose
+// records share one region of LDS (FP64), pipelined over tiles.
+constexpr int32_t kFormOne = 0, kFormSweeps = 1, kFormPipe = 2;
 
 // Device pointers of one context.  Per-particle data is in Hilbert order;
 // SoA fields have stride np (a multiple of kSlice), component c of particle
@@ -161,6 +175,7 @@ struct DevState {
     const int32_t* halo;      // [n_tiles][halo_cap]
     const int32_t* halo_cnt;  // [n_tiles]
     const uint16_t* lcol;
+    const uint32_t* pslot;    // [np][kPackWords] the first neighbours' local slots, packed
     int32_t halo_cap;
     int32_t staged;           // 1 when the staged force pass is in use
     int32_t lds_slots;        // record slots of the staged kernels' LDS images (tile + largest halo)
@@ -171,6 +186,8 @@ struct DevState {
     int32_t var_h;            // 1 if a specimen has graded spacing (per-particle support)
     int32_t contact;          // 1 if a specimen has penalty contact
     int32_t tile;             // particles per tile of the staged force pass (<= kTile)
+    int32_t form_b;           // form of the staged force pass (kForm*), over grid_b workgroups
+    int32_t grid_b, pad4_;
     // The staged deformation pass's tiles: the force pass's (the same
     // arrays), or a size of their own (arrays of their own).
     int32_t staged_lds_a;     // 1 when the tile records of the deformation pass fit LDS
@@ -223,13 +240,19 @@ hipError_t launch_build_fill(DevState& s, const BuildBuffers& b, hipStream_t st)
 // Halo lists and local slots for tiles of T particles (halo_cap = T k_cap)
 // into the given arrays; the largest halo is max-reduced into s.err[4].
 hipError_t launch_halo(const DevState& s, int k_cap, int T, int32_t* halo, int32_t* halo_cnt,
-                       uint16_t* lcol, hipStream_t st);
+                       uint16_t* lcol, uint32_t* pslot, hipStream_t st);
 hipError_t prepare_staged(size_t lds_bytes_b);
+hipError_t staged_blocks_per_cu(bool mixed, int threads, size_t lds_bytes, int* out);
+// LDS bytes per slot of the staged force pass's forms, and the most neighbours
+// a particle may have in the pipelined one.
+size_t staged_one_bytes(bool mixed, bool var_h);
+size_t staged_sweep_bytes(bool var_h);
+size_t staged_pipe_bytes(bool mixed);
+int staged_pipe_neighbours();
 // Largest tile the staged force pass runs with `sub` lanes per particle.
 int staged_tile_max(int sub);
-// LDS bytes per slot of the staged force pass and the staged deformation pass
-// (graded spacing adds the slot's support radius).
-size_t staged_record_bytes(bool mixed, bool var_h);
+// LDS bytes per slot of the staged deformation pass (graded spacing adds the
+// slot's support radius).
 size_t staged_a_record_bytes(bool var_h);
 hipError_t launch_shape_and_init(const DevState& s, bool mixed, hipStream_t st);
 hipError_t launch_get_field(const DevState& s, int field, int parity, bool mixed, double* dst,

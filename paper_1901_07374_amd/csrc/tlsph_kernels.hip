@@ -460,7 +460,7 @@ __global__ void k_init(DevState s) {
         GHRec<double> h;
         for (int k = 0; k < 9; ++k) { g.q[k] = 0.0; h.h[k] = 0.0; }
         g.omd = 1.0 - D0;
-        h.pad = 0.0;
+        h.vw = s.XV[p].w * g.omd;
         s.GQ[p] = g;
         s.GH[p] = h;
     } else {
@@ -468,7 +468,7 @@ __global__ void k_init(DevState s) {
         GHRec<float> h;
         for (int k = 0; k < 9; ++k) { g.q[k] = 0.0f; h.h[k] = 0.0f; }
         g.omd = (float)(1.0 - D0);
-        h.pad = 0.0f;
+        h.vw = float(s.XV[p].w) * g.omd;
         s.GQ32[p] = g;
         s.GH32[p] = h;
     }
@@ -515,7 +515,8 @@ hipError_t launch_build_count(DevState& s, const BuildBuffers& b, hipStream_t st
 // 688.
 __global__ void __launch_bounds__(256) k_halo(DevState s, int E, int32_t* __restrict__ halo,
                                               int32_t* __restrict__ halo_cnt,
-                                              uint16_t* __restrict__ lcol) {
+                                              uint16_t* __restrict__ lcol,
+                                              uint32_t* __restrict__ pslot) {
     extern __shared__ int32_t sh[];
     int32_t* set = sh;            // [E]
     int32_t* hl = sh + E;         // [E]
@@ -596,11 +597,29 @@ __global__ void __launch_bounds__(256) k_halo(DevState s, int E, int32_t* __rest
             }
             lp[(int64_t)k * kSlice] = (uint16_t)loc;
         }
+        if (!pslot) return;
+        // the first kPackGroups groups of kSub neighbours as they are read (see
+        // Slots), the first neighbour (or the particle) past the last
+        uint32_t o[kPackWords];
+#pragma unroll
+        for (int w = 0; w < kPackWords; ++w) {
+            o[w] = 0;
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                const int e = 2 * w + q, k = (e % kPackGroups) * kSub + e / kPackGroups;
+                const uint32_t m = cnt > 0 ? lp[(int64_t)(k < cnt ? k : 0) * kSlice] : (uint32_t)tid;
+                o[w] |= m << (16 * q);
+            }
+        }
+        uint4* out = reinterpret_cast<uint4*>(pslot + p * kPackWords);
+#pragma unroll
+        for (int w = 0; w < kPackWords / 4; ++w)
+            out[w] = uint4{o[4 * w], o[4 * w + 1], o[4 * w + 2], o[4 * w + 3]};
     }
 }
 
 hipError_t launch_halo(const DevState& s, int k_cap, int T, int32_t* halo, int32_t* halo_cnt,
-                       uint16_t* lcol, hipStream_t st) {
+                       uint16_t* lcol, uint32_t* pslot, hipStream_t st) {
     if (T < 1 || T > kTile) return hipErrorInvalidValue;
     int E = 256;
     while (E < T * k_cap) E <<= 1;
@@ -612,7 +631,7 @@ hipError_t launch_halo(const DevState& s, int k_cap, int T, int32_t* halo, int32
     t.tile = T;
     t.halo_cap = T * k_cap;
     const unsigned tiles = (unsigned)((s.n + T - 1) / T);
-    k_halo<<<tiles, 256, lds, st>>>(t, E, halo, halo_cnt, lcol);
+    k_halo<<<tiles, 256, lds, st>>>(t, E, halo, halo_cnt, lcol, pslot);
     return hipGetLastError();
 }
 
@@ -691,6 +710,40 @@ __device__ __forceinline__ int64_t work_tile(const int32_t* list, const int32_t*
     return t < n_tiles ? t : -1;
 }
 
+// The tiles of one workgroup of the staged force pass, whose workgroups each
+// run several: XCD x takes one contiguous run of the tiles (of the running
+// specimens' tiles, under run control), and its workgroups walk it side by
+// side, so that the tiles in flight on an XCD are neighbours.  -1 past the end.
+struct TileWalk {
+    const int32_t* list;
+    int32_t n_tiles;
+    int64_t k, end, step;
+    __device__ TileWalk(const int32_t* list_, const int32_t* count, int64_t n_tiles_)
+        : list(list_), n_tiles((int32_t)n_tiles_) {
+        constexpr int64_t kXcd = 8;
+        const int64_t nw = list ? (int64_t)__builtin_amdgcn_readfirstlane(*count) : n_tiles_;
+        const int64_t b = blockIdx.x, g = gridDim.x;
+        const int64_t x = b % kXcd, nx = g < kXcd ? g : kXcd;   // XCDs with a workgroup
+        const int64_t q = nw / nx, r = nw % nx;
+        const int64_t beg = x * q + (x < r ? x : r);
+        end = beg + q + (x < r ? 1 : 0);
+        step = g / kXcd + (x < g % kXcd ? 1 : 0);   // workgroups on this XCD
+        k = beg + b / kXcd;
+    }
+    // The next tile as it is loaded (a per-lane value, the same in every lane),
+    // to be settled once the load has arrived.
+    __device__ int32_t load() {
+        int32_t t = -1;
+        if (k < end) t = list ? list[k] : (int32_t)k;
+        k += step;
+        return t;
+    }
+    __device__ int32_t settle(int32_t t) const {
+        const int32_t u = __builtin_amdgcn_readfirstlane(t);
+        return u < n_tiles ? u : -1;   // (a list of this tile size has none beyond)
+    }
+};
+
 // A specimen that run control has stopped keeps its state.
 __device__ __forceinline__ bool frozen(const DevState& s, int sp) {
     return s.done != nullptr && s.done[sp] != kRunning;
@@ -749,9 +802,20 @@ __device__ __forceinline__ LRecB<R> make_recb(const D4& xv, const GQRec<R>& g, c
     return r;
 }
 
+// Sums of the force pass over a particle's neighbours: the stress sums a and b
+// and the hourglass sum g.
+template <typename R>
+struct StressAcc {
+    R a0 = 0, a1 = 0, a2 = 0, b0 = 0, b1 = 0, b2 = 0;
+};
+template <typename R>
+struct HgAcc {
+    R g0 = 0, g1 = 0, g2 = 0;
+};
 template <typename R>
 struct ForceAcc {
-    R a0 = 0, a1 = 0, a2 = 0, b0 = 0, b1 = 0, b2 = 0, g0 = 0, g1 = 0, g2 = 0;
+    StressAcc<R> st;
+    HgAcc<R> hg;
 };
 
 // 1/sqrt(x) and 1/x for x > 0 finite (the refinement of rsqrt_nr and rcp_nr
@@ -787,17 +851,25 @@ __device__ __forceinline__ float rcp_pos(float x) {
 // spacing (kVarH) each pair has its own support h_ij = (h_i + h_j) / 2, so
 // the constant factors c / h_ij and c = 8 / (pi h_ij^3) enter per pair and the
 // finish applies none.
-template <typename R, bool kVarH = false>
-__device__ __forceinline__ void force_pair(const LRecB<R>& ni, const LRecB<R>& nj, R inv_h,
-                                           ForceAcc<R>& A, bool live = true) {
+
+// Geometry of a pair: X_ij, 1 / r, w, and gv = V_j s / r.
+template <typename R>
+struct PairGeom {
+    R dx, dy, dz, ir, w, gv;
+};
+template <typename R, bool kVarH>
+__device__ __forceinline__ PairGeom<R> pair_geom(double xi, double yi, double zi, double xj,
+                                                 double yj, double zj, R Vj, double hsi,
+                                                 double hsj, R inv_h, bool live) {
     // a padding slot (live = false) gets 1/r = 1/|x|^2 = 0: every term it
     // adds is an exact zero
-    const R dx = R(nj.x - ni.x), dy = R(nj.y - ni.y), dz = R(nj.z - ni.z);
-    const R r2 = fma(dx, dx, fma(dy, dy, dz * dz));
+    PairGeom<R> p;
+    p.dx = R(xj - xi), p.dy = R(yj - yi), p.dz = R(zj - zi);
+    const R r2 = fma(p.dx, p.dx, fma(p.dy, p.dy, p.dz * p.dz));
     const R ir = live ? rsqrt_pos(r2) : R(0);
     R kg = R(1), kw = R(1);
     if constexpr (kVarH) {
-        inv_h = rcp_nr(R(0.5 * (ni.hs + nj.hs)));
+        inv_h = rcp_nr(R(0.5 * (hsi + hsj)));
         kw = R(8.0 / M_PI) * inv_h * inv_h * inv_h;
         kg = kw * inv_h;
     }
@@ -823,38 +895,73 @@ __device__ __forceinline__ void force_pair(const LRecB<R>& ni, const LRecB<R>& n
         w = (a + a) * a2;
         sl = R(-6) * a2;
     }
-    const R Vj = nj.V0;
     R gv = sl * ir * Vj;
     if constexpr (kVarH) {
         gv *= kg;
         w *= kw;
     }
-    const R gx = gv * dx, gy = gv * dy, gz = gv * dz;
-    A.a0 = fma(nj.omd, gx, A.a0); A.a1 = fma(nj.omd, gy, A.a1); A.a2 = fma(nj.omd, gz, A.a2);
-    A.b0 = fma(nj.q[0], gx, fma(nj.q[1], gy, fma(nj.q[2], gz, A.b0)));
-    A.b1 = fma(nj.q[3], gx, fma(nj.q[4], gy, fma(nj.q[5], gz, A.b1)));
-    A.b2 = fma(nj.q[6], gx, fma(nj.q[7], gy, fma(nj.q[8], gz, A.b2)));
-    const R du0 = R(nj.ux - ni.ux), du1 = R(nj.uy - ni.uy), du2 = R(nj.uz - ni.uz);
+    p.ir = ir;
+    p.w = w;
+    p.gv = gv;
+    return p;
+}
+
+// Stress part of a pair: g = V_j s X_ij / r, omd and q the neighbour's 1 - D
+// and Q.
+template <typename R>
+__device__ __forceinline__ void stress_pair(R gx, R gy, R gz, R omd, const R (&q)[9],
+                                            StressAcc<R>& A) {
+    A.a0 = fma(omd, gx, A.a0); A.a1 = fma(omd, gy, A.a1); A.a2 = fma(omd, gz, A.a2);
+    A.b0 = fma(q[0], gx, fma(q[1], gy, fma(q[2], gz, A.b0)));
+    A.b1 = fma(q[3], gx, fma(q[4], gy, fma(q[5], gz, A.b1)));
+    A.b2 = fma(q[6], gx, fma(q[7], gy, fma(q[8], gz, A.b2)));
+}
+
+// Hourglass part of a pair: vw = V_j (1 - D_j), du = u_j - u_i.
+template <typename R>
+__device__ __forceinline__ void hg_pair(const PairGeom<R>& p, R vw, R du0, R du1, R du2,
+                                        const R (&hi)[9], const R (&hj)[9], bool live,
+                                        HgAcc<R>& A) {
+    const R dx = p.dx, dy = p.dy, dz = p.dz;
     const R x0 = dx + du0, x1 = dy + du1, x2 = dz + du2;
     const R rc2 = fma(x0, x0, fma(x1, x1, x2 * x2));
     const R irc2 = (live && rc2 > R(0)) ? rcp_pos(rc2) : R(0);
-    const R v0 = fma(ni.h[0] + nj.h[0], dx, fma(ni.h[1] + nj.h[1], dy, (ni.h[2] + nj.h[2]) * dz));
-    const R v1 = fma(ni.h[3] + nj.h[3], dx, fma(ni.h[4] + nj.h[4], dy, (ni.h[5] + nj.h[5]) * dz));
-    const R v2 = fma(ni.h[6] + nj.h[6], dx, fma(ni.h[7] + nj.h[7], dy, (ni.h[8] + nj.h[8]) * dz));
+    const R v0 = fma(hi[0] + hj[0], dx, fma(hi[1] + hj[1], dy, (hi[2] + hj[2]) * dz));
+    const R v1 = fma(hi[3] + hj[3], dx, fma(hi[4] + hj[4], dy, (hi[5] + hj[5]) * dz));
+    const R v2 = fma(hi[6] + hj[6], dx, fma(hi[7] + hj[7], dy, (hi[8] + hj[8]) * dz));
     const R hx = fma(v0, x0, fma(v1, x1, v2 * x2));
     const R ux = fma(du0, x0, fma(du1, x1, du2 * x2));
     const R ex = fma(R(0.5), hx, -ux);
-    const R c = Vj * nj.omd * w * ex * (ir * ir) * irc2;
+    const R c = vw * p.w * ex * (p.ir * p.ir) * irc2;
     A.g0 = fma(c, x0, A.g0); A.g1 = fma(c, x1, A.g1); A.g2 = fma(c, x2, A.g2);
 }
 
+template <typename R, bool kVarH = false>
+__device__ __forceinline__ void force_pair(const LRecB<R>& ni, const LRecB<R>& nj, R inv_h,
+                                           ForceAcc<R>& A, bool live = true) {
+    const PairGeom<R> p = pair_geom<R, kVarH>(ni.x, ni.y, ni.z, nj.x, nj.y, nj.z, nj.V0, ni.hs,
+                                              nj.hs, inv_h, live);
+    stress_pair<R>(p.gv * p.dx, p.gv * p.dy, p.gv * p.dz, nj.omd, nj.q, A.st);
+    hg_pair<R>(p, nj.V0 * nj.omd, R(nj.ux - ni.ux), R(nj.uy - ni.uy), R(nj.uz - ni.uz), ni.h, nj.h,
+               live, A.hg);
+}
+
 template <typename R>
-__device__ __forceinline__ ForceAcc<R> acc_sum(const ForceAcc<R>& x, const ForceAcc<R>& y) {
-    ForceAcc<R> r;
+__device__ __forceinline__ StressAcc<R> acc_sum(const StressAcc<R>& x, const StressAcc<R>& y) {
+    StressAcc<R> r;
     r.a0 = x.a0 + y.a0; r.a1 = x.a1 + y.a1; r.a2 = x.a2 + y.a2;
     r.b0 = x.b0 + y.b0; r.b1 = x.b1 + y.b1; r.b2 = x.b2 + y.b2;
+    return r;
+}
+template <typename R>
+__device__ __forceinline__ HgAcc<R> acc_sum(const HgAcc<R>& x, const HgAcc<R>& y) {
+    HgAcc<R> r;
     r.g0 = x.g0 + y.g0; r.g1 = x.g1 + y.g1; r.g2 = x.g2 + y.g2;
     return r;
+}
+template <typename R>
+__device__ __forceinline__ ForceAcc<R> acc_sum(const ForceAcc<R>& x, const ForceAcc<R>& y) {
+    return ForceAcc<R>{acc_sum(x.st, y.st), acc_sum(x.hg, y.hg)};
 }
 
 // The value of lane l ^ m (m = 1 or 2) within each group of four lanes, by a
@@ -876,12 +983,65 @@ __device__ __forceinline__ double quad_xor(double v) {
 }
 
 template <int M, typename R>
-__device__ __forceinline__ ForceAcc<R> acc_xor(const ForceAcc<R>& x) {
-    ForceAcc<R> r;
+__device__ __forceinline__ StressAcc<R> acc_xor(const StressAcc<R>& x) {
+    StressAcc<R> r;
     r.a0 = quad_xor<M>(x.a0); r.a1 = quad_xor<M>(x.a1); r.a2 = quad_xor<M>(x.a2);
     r.b0 = quad_xor<M>(x.b0); r.b1 = quad_xor<M>(x.b1); r.b2 = quad_xor<M>(x.b2);
+    return r;
+}
+template <int M, typename R>
+__device__ __forceinline__ HgAcc<R> acc_xor(const HgAcc<R>& x) {
+    HgAcc<R> r;
     r.g0 = quad_xor<M>(x.g0); r.g1 = quad_xor<M>(x.g1); r.g2 = quad_xor<M>(x.g2);
     return r;
+}
+template <int M, typename R>
+__device__ __forceinline__ ForceAcc<R> acc_xor(const ForceAcc<R>& x) {
+    return ForceAcc<R>{acc_xor<M>(x.st), acc_xor<M>(x.hg)};
+}
+
+// The partial sums of a particle's S lanes combined as (p0 + p1) + (p2 + p3)
+// (A: the lane's kSub / S partials; every lane gets the result).
+template <int S, typename Acc>
+__device__ __forceinline__ Acc combine_partials(const Acc (&A)[kSub / S]) {
+    if constexpr (S == 1) {
+        return acc_sum(acc_sum(A[0], A[1]), acc_sum(A[2], A[3]));
+    } else if constexpr (S == 2) {
+        const Acc x = acc_sum(A[0], acc_xor<1>(A[0]));   // p0 + p1
+        const Acc y = acc_sum(A[1], acc_xor<1>(A[1]));   // p2 + p3
+        return acc_sum(x, y);
+    } else {
+        const Acc x = acc_sum(A[0], acc_xor<1>(A[0]));   // p0 + p1 | p2 + p3
+        return acc_sum(x, acc_xor<2>(x));
+    }
+}
+
+// A lane's share of a particle's first kPackGroups kSub neighbours as local
+// slots, two to a word: list t of a lane (neighbours sub + S t, + kSub, ...) is
+// kPackGroups consecutive entries of the particle's record, so a lane loads it
+// with one instruction where the sliced list takes one per entry.
+template <int S>
+struct Slots {
+    static constexpr int NP = kSub / S;
+    static constexpr int W = kPackGroups / 2;
+    uint32_t w[NP][W];
+    __device__ int at(int g, int t) const {
+        return (int)((g & 1) ? w[t][g >> 1] >> 16 : w[t][g >> 1] & 0xffffu);
+    }
+};
+template <int S>
+__device__ __forceinline__ Slots<S> load_slots(const uint32_t* __restrict__ pslot, int64_t i, int sub) {
+    static_assert(kPackGroups == 6 && kPackWords == 12, "three words a list");
+    struct alignas(4) W3 {
+        uint32_t a, b, c;
+    };
+    Slots<S> f;
+#pragma unroll
+    for (int t = 0; t < Slots<S>::NP; ++t) {
+        const W3 v = *reinterpret_cast<const W3*>(pslot + i * kPackWords + 3 * (sub + S * t));
+        f.w[t][0] = v.a; f.w[t][1] = v.b; f.w[t][2] = v.c;
+    }
+    return f;
 }
 
 // Pair sums of one particle in the canonical order of the force pass:
@@ -890,71 +1050,26 @@ __device__ __forceinline__ ForceAcc<R> acc_xor(const ForceAcc<R>& x) {
 // particle (S = 1, 2 or 4), lane `sub` holding partials sub, sub + S, ...;
 // every S rounds identically.  All lanes of the wave must call this (the
 // partials are exchanged across lanes); lanes without a particle pass cnt = 0.
-// The neighbour indices of a lane's first G groups (neighbours sub, sub + S,
-// ... below G kSub), loaded apart so that a kernel can issue them before its
-// staging: the pair loop then runs those groups without waiting on memory.
-// Local slots (below 2^16, kPack) go two to a register.
-template <int S, int G, bool kPack = false>
-struct FirstIdx {
-    static constexpr int NP = kSub / S;
-    static constexpr int E = G * NP;   // entries, group-major
-    uint32_t w[kPack ? (E + 1) / 2 : E];
-    __device__ int at(int g, int t) const {
-        const int e = g * NP + t;
-        if constexpr (kPack)
-            return (int)((e & 1) ? w[e >> 1] >> 16 : w[e >> 1] & 0xffffu);
-        else
-            return (int)w[e];
-    }
-};
-template <int S, int G, bool kPack = false, typename IdxOf>
-__device__ __forceinline__ FirstIdx<S, G, kPack> first_indices(int cnt, int sub, IdxOf idx) {
-    using FI = FirstIdx<S, G, kPack>;
-    FI f;
-    const auto at = [&](int e) {
-        const int k = (e / FI::NP) * kSub + sub + S * (e % FI::NP);
-        return (uint32_t)idx(k < cnt ? k : 0);
-    };
-#pragma unroll
-    for (int e = 0; e < FI::E; e += kPack ? 2 : 1) {
-        if constexpr (kPack)
-            f.w[e >> 1] = at(e) | (e + 1 < FI::E ? at(e + 1) << 16 : 0u);
-        else
-            f.w[e] = at(e);
-    }
-    return f;
-}
-
-template <typename R, int S, bool kVarH = false, int G, bool kPack, typename IdxOf, typename RecOf>
+// Indices run one group of kSub ahead of the arithmetic.
+template <typename R, int S, bool kVarH = false, typename IdxOf, typename RecOf>
 __device__ __forceinline__ ForceAcc<R> pair_sums(const LRecB<R>& ni, int cnt, int sub, R inv_h,
-                                                 IdxOf idx, RecOf rec,
-                                                 const FirstIdx<S, G, kPack>& first) {
+                                                 IdxOf idx, RecOf rec) {
     static_assert(kSub == 4 && (S == 1 || S == 2 || S == 4), "canonical order has 4 partials");
-    static_assert(G >= 1, "at least the first group is preloaded");
     constexpr int NP = kSub / S;
     ForceAcc<R> A[NP];
-    // the group after the preloaded ones goes out first: its latency is spent
-    // behind them (longer lists then run their indices one group of kSub
-    // ahead of the arithmetic)
-    int q[NP];
+    int first[NP], q[NP];
 #pragma unroll
     for (int t = 0; t < NP; ++t) {
-        const int k = G * kSub + sub + S * t;
-        q[t] = idx(k < cnt ? k : 0);
+        const int k = sub + S * t;
+        first[t] = idx(k < cnt ? k : 0);
+        q[t] = idx(kSub + k < cnt ? kSub + k : 0);
     }
-    // the preloaded groups, unrolled (a lane past its count is masked off)
+    if (0 < cnt) {
 #pragma unroll
-    for (int g = 0; g < G; ++g) {
-        const int k0 = g * kSub;
-        if (k0 < cnt) {
-#pragma unroll
-            for (int t = 0; t < NP; ++t) {
-                const int k = k0 + sub + S * t;
-                force_pair<R, kVarH>(ni, rec(first.at(g, t)), inv_h, A[t], k < cnt);
-            }
-        }
+        for (int t = 0; t < NP; ++t)
+            force_pair<R, kVarH>(ni, rec(first[t]), inv_h, A[t], sub + S * t < cnt);
     }
-    for (int k0 = G * kSub; k0 < cnt; k0 += kSub) {
+    for (int k0 = kSub; k0 < cnt; k0 += kSub) {
         int cur[NP];
 #pragma unroll
         for (int t = 0; t < NP; ++t) {
@@ -968,16 +1083,7 @@ __device__ __forceinline__ ForceAcc<R> pair_sums(const LRecB<R>& ni, int cnt, in
             force_pair<R, kVarH>(ni, rec(cur[t]), inv_h, A[t], k < cnt);
         }
     }
-    if constexpr (S == 1) {
-        return acc_sum(acc_sum(A[0], A[1]), acc_sum(A[2], A[3]));
-    } else if constexpr (S == 2) {
-        const ForceAcc<R> x = acc_sum(A[0], acc_xor<1>(A[0]));   // p0 + p1
-        const ForceAcc<R> y = acc_sum(A[1], acc_xor<1>(A[1]));   // p2 + p3
-        return acc_sum(x, y);
-    } else {
-        const ForceAcc<R> x = acc_sum(A[0], acc_xor<1>(A[0]));   // p0 + p1 | p2 + p3
-        return acc_sum(x, acc_xor<2>(x));
-    }
+    return combine_partials<S>(A);
 }
 
 // Penalty contact force on particle i at its position (xi, yi, zi) at t^n:
@@ -1027,84 +1133,131 @@ __device__ __forceinline__ void contact_force(const DevState& s, int64_t i, int 
 // pair sums so that their latency is spent behind them.
 struct FinishIn {
     double D, V, vx, vy, vz;
-    double grad_k, hg_k, dt, dt_rho0;
-    int32_t bc, wall;
+    int32_t bc;
 };
-template <bool kVarH = false>
-__device__ __forceinline__ FinishIn finish_in(const DevState& s, int64_t i, const DevSpec& P) {
+// The velocity ramp 1 - exp(-t / tau) of the boundary group and specimen a wave
+// met last (the same for every particle of a launch: the pipelined pass's waves
+// finish many tiles, mostly of one group).
+struct Ramp {
+    int32_t group = -1, sp = -1;
+    double value = 0.0;
+};
+__device__ __forceinline__ FinishIn finish_in(const DevState& s, int64_t i, double V) {
     const D4 v = s.VW[i];
-    // graded spacing: the pair sums carry the kernel's constant factors
-    return FinishIn{s.D[i], s.XV[i].w, v.x, v.y, v.z, kVarH ? 1.0 : P.grad_k,
-                    kVarH ? -P.hg_alpha * P.E : P.hg_k, P.dt, P.dt_rho0, s.bc[i], P.has_wall};
+    return FinishIn{s.D[i], V, v.x, v.y, v.z, s.bc[i]};
+}
+
+// A value that is the same in every active lane, as a scalar.
+__device__ __forceinline__ double uniform(double x) {
+    const long long b = __double_as_longlong(x);
+    const unsigned lo = __builtin_amdgcn_readfirstlane((int)(b & 0xffffffffll));
+    const unsigned hi = __builtin_amdgcn_readfirstlane((int)(b >> 32));
+    return __longlong_as_double(((long long)hi << 32) | lo);
 }
 
 // Nodal force, kick, prescribed velocities, failed particles at rest, drift,
 // rigid wall; stores v, V0 (1 - D), u^{n+1} and (for groups) the force.  The
 // force per unit volume f / V_i is formed first: the kick is dt / rho0 times
-// it (m = rho0 V_i).
-template <typename R>
-__device__ __forceinline__ void force_finish(const DevState& s, int64_t i, int par, const DevSpec& P,
-                                             int sp, const LRecB<R>& ni, const ForceAcc<R>& A,
-                                             const FinishIn& fin) {
+// it (m = rho0 V_i).  The lanes of a wave take turns by specimen, and within
+// it by boundary group (one turn each unless the wave straddles two), so that
+// both records arrive by scalar loads, which the CU's scalar cache keeps: per
+// lane they would be two more dependent trips to memory at the end of a tile.
+// kTwo: two adjacent lanes (sub 0, 1) hold the particle's sums and both come
+// here; each stores half of every record, so that a wave's stores are contiguous.
+template <typename R, bool kVarH = false, bool kTwo = false>
+__device__ __forceinline__ void force_finish(const DevState& s, int64_t i, int par, int sp_lane,
+                                             const LRecB<R>& ni, const ForceAcc<R>& A,
+                                             const FinishIn& fin, Ramp& ramp, int sub = 0) {
     const int64_t np = s.np;
-    const double Di = fin.D;
-    const R omDi = R(1.0 - Di);
-    const R ck = R(fin.grad_k);
-    const R hgk = R(fin.hg_k) * omDi;
-    const double Vi = fin.V;
-    double fv0 = double(ck * (ni.q[0] * A.a0 + ni.q[1] * A.a1 + ni.q[2] * A.a2 + omDi * A.b0) + hgk * A.g0);
-    double fv1 = double(ck * (ni.q[3] * A.a0 + ni.q[4] * A.a1 + ni.q[5] * A.a2 + omDi * A.b1) + hgk * A.g1);
-    double fv2 = double(ck * (ni.q[6] * A.a0 + ni.q[7] * A.a1 + ni.q[8] * A.a2 + omDi * A.b2) + hgk * A.g2);
-    if (s.av) {   // the artificial viscous force of the last deformation pass
-        const double iv = rcp_nr(Vi);
-        fv0 += s.fvisc[i] * iv;
-        fv1 += s.fvisc[np + i] * iv;
-        fv2 += s.fvisc[2 * np + i] * iv;
-    }
-    if (s.contact) {   // penalty contact with the listed candidates
-        double fc[3];
-        contact_force(s, i, par, sp, ni.x + ni.ux, ni.y + ni.uy, ni.z + ni.uz, Di, fc);
-        const double iv = rcp_nr(Vi);
-        fv0 += fc[0] * iv;
-        fv1 += fc[1] * iv;
-        fv2 += fc[2] * iv;
-    }
-    const double dt = fin.dt;
-    double v[3] = {fin.vx + fin.dt_rho0 * fv0, fin.vy + fin.dt_rho0 * fv1,
-                   fin.vz + fin.dt_rho0 * fv2};
-    const double xi = ni.x, yi = ni.y, zi = ni.z;
-    const int g = fin.bc;
-    if (g >= 0) {
-        const DevBC& B = s.bcs[g];
-        const double th = s.t[sp] + 0.5 * dt;
-        const double ramp = B.tau > 0.0 ? 1.0 - exp(-th / B.tau) : 1.0;
+    for (;;) {
+        const int sp = __builtin_amdgcn_readfirstlane(sp_lane);
+        if (sp != sp_lane) continue;
+        if (frozen(s, sp)) return;
+        const DevSpec& P = s.specs[sp];
+        const double Di = fin.D;
+        const R omDi = R(1.0 - Di);
+        // (graded spacing: the pair sums carry the kernel's constant factors)
+        const R ck = R(kVarH ? 1.0 : P.grad_k);
+        const R hgk = R(kVarH ? -P.hg_alpha * P.E : P.hg_k) * omDi;
+        const double Vi = fin.V;
+        const StressAcc<R>& a = A.st;
+        const HgAcc<R>& g = A.hg;
+        double fv0 = double(ck * (ni.q[0] * a.a0 + ni.q[1] * a.a1 + ni.q[2] * a.a2 + omDi * a.b0) + hgk * g.g0);
+        double fv1 = double(ck * (ni.q[3] * a.a0 + ni.q[4] * a.a1 + ni.q[5] * a.a2 + omDi * a.b1) + hgk * g.g1);
+        double fv2 = double(ck * (ni.q[6] * a.a0 + ni.q[7] * a.a1 + ni.q[8] * a.a2 + omDi * a.b2) + hgk * g.g2);
+        if (s.av) {   // the artificial viscous force of the last deformation pass
+            const double iv = rcp_nr(Vi);
+            fv0 += s.fvisc[i] * iv;
+            fv1 += s.fvisc[np + i] * iv;
+            fv2 += s.fvisc[2 * np + i] * iv;
+        }
+        if (s.contact) {   // penalty contact with the listed candidates
+            double fc[3];
+            contact_force(s, i, par, sp, ni.x + ni.ux, ni.y + ni.uy, ni.z + ni.uz, Di, fc);
+            const double iv = rcp_nr(Vi);
+            fv0 += fc[0] * iv;
+            fv1 += fc[1] * iv;
+            fv2 += fc[2] * iv;
+        }
+        const double dt = P.dt, dt_rho0 = P.dt_rho0;
+        double v[3] = {fin.vx + dt_rho0 * fv0, fin.vy + dt_rho0 * fv1, fin.vz + dt_rho0 * fv2};
+        const double xi = ni.x, yi = ni.y, zi = ni.z;
+        const int grp = fin.bc;
+        if (grp >= 0) {
+            for (;;) {
+                const int gw = __builtin_amdgcn_readfirstlane(grp);
+                if (gw != grp) continue;
+                const DevBC& B = s.bcs[gw];
+                if (gw != ramp.group || sp != ramp.sp) {
+                    const double th = s.t[sp] + 0.5 * dt;
+                    const double r = B.tau > 0.0 ? 1.0 - exp(-th / B.tau) : 1.0;
+                    ramp.group = gw;
+                    ramp.sp = sp;
+                    ramp.value = uniform(r);
+                }
 #pragma unroll
-        for (int c = 0; c < 3; ++c)
-            if (B.mask & (1 << c))
-                v[c] = B.v_max[c] * ramp + (B.grad[3 * c] * xi + B.grad[3 * c + 1] * yi +
-                                            B.grad[3 * c + 2] * zi);
-    }
-    if (Di >= 1.0) v[0] = v[1] = v[2] = 0.0;
-    double un[3] = {ni.ux + dt * v[0], ni.uy + dt * v[1], ni.uz + dt * v[2]};
-    if (fin.wall) {
-        const double xw[3] = {xi + un[0], yi + un[1], zi + un[2]};
-        const double dn = xw[0] * P.wall_n[0] + xw[1] * P.wall_n[1] + xw[2] * P.wall_n[2] - P.wall_d;
-        if (dn < 0.0) {
-            un[0] = (xw[0] - dn * P.wall_n[0]) - xi;
-            un[1] = (xw[1] - dn * P.wall_n[1]) - yi;
-            un[2] = (xw[2] - dn * P.wall_n[2]) - zi;
-            const double vn = v[0] * P.wall_n[0] + v[1] * P.wall_n[1] + v[2] * P.wall_n[2];
-            if (vn < 0.0) {
-                v[0] -= vn * P.wall_n[0];
-                v[1] -= vn * P.wall_n[1];
-                v[2] -= vn * P.wall_n[2];
+                for (int c = 0; c < 3; ++c)
+                    if (B.mask & (1 << c))
+                        v[c] = B.v_max[c] * ramp.value + (B.grad[3 * c] * xi + B.grad[3 * c + 1] * yi +
+                                                    B.grad[3 * c + 2] * zi);
+                break;
             }
         }
-    }
-    s.VW[i] = D4{v[0], v[1], v[2], Vi * (1.0 - Di)};
-    s.U[par ^ 1][i] = D4{un[0], un[1], un[2], 0.0};
-    if ((s.flags & kFlagStoreForce) || g >= 0) {
-        s.force[i] = Vi * fv0; s.force[np + i] = Vi * fv1; s.force[2 * np + i] = Vi * fv2;
+        if (Di >= 1.0) v[0] = v[1] = v[2] = 0.0;
+        double un[3] = {ni.ux + dt * v[0], ni.uy + dt * v[1], ni.uz + dt * v[2]};
+        if (P.has_wall) {
+            const double xw[3] = {xi + un[0], yi + un[1], zi + un[2]};
+            const double dn = xw[0] * P.wall_n[0] + xw[1] * P.wall_n[1] + xw[2] * P.wall_n[2] - P.wall_d;
+            if (dn < 0.0) {
+                un[0] = (xw[0] - dn * P.wall_n[0]) - xi;
+                un[1] = (xw[1] - dn * P.wall_n[1]) - yi;
+                un[2] = (xw[2] - dn * P.wall_n[2]) - zi;
+                const double vn = v[0] * P.wall_n[0] + v[1] * P.wall_n[1] + v[2] * P.wall_n[2];
+                if (vn < 0.0) {
+                    v[0] -= vn * P.wall_n[0];
+                    v[1] -= vn * P.wall_n[1];
+                    v[2] -= vn * P.wall_n[2];
+                }
+            }
+        }
+        const double w = Vi * (1.0 - Di);
+        const bool keep = (s.flags & kFlagStoreForce) || grp >= 0;
+        if constexpr (kTwo) {
+            reinterpret_cast<double2*>(s.VW)[2 * i + sub] = sub ? double2{v[2], w} : double2{v[0], v[1]};
+            reinterpret_cast<double2*>(s.U[par ^ 1])[2 * i + sub] =
+                sub ? double2{un[2], 0.0} : double2{un[0], un[1]};
+            if (keep) {
+                s.force[sub * np + i] = Vi * (sub ? fv1 : fv0);
+                if (!sub) s.force[2 * np + i] = Vi * fv2;
+            }
+        } else {
+            s.VW[i] = D4{v[0], v[1], v[2], w};
+            s.U[par ^ 1][i] = D4{un[0], un[1], un[2], 0.0};
+            if (keep) {
+                s.force[i] = Vi * fv0; s.force[np + i] = Vi * fv1; s.force[2 * np + i] = Vi * fv2;
+            }
+        }
+        return;
     }
 }
 
@@ -1138,7 +1291,7 @@ k_pass_b(DevState s, int par) {
     const R inv_h = R(P.inv_h);
     const bool live = in && !frozen(s, sp);
     const int cnt = live ? s.nnb[i] : 0;
-    const FinishIn fin = finish_in<kVarH>(s, ii, P);
+    const FinishIn fin = finish_in(s, ii, XV[ii].w);
     const int32_t* __restrict__ cp = s.col + s.slice_ptr[ii / kSlice] + (ii % kSlice);
     const auto idx = [&](int k) { return (int)cp[(int64_t)k * kSlice]; };
     const ForceAcc<R> A = pair_sums<R, S, kVarH>(
@@ -1147,23 +1300,120 @@ k_pass_b(DevState s, int par) {
             LRecB<R> r = make_recb<R>(XV[j], GQ[j], GH[j], Uc[j]);
             if constexpr (kVarH) r.hs = s.hs[j];
             return r;
-        },
-        first_indices<S, 1>(cnt, sub, idx));
+        });
     // the particle's own Q is needed only now: reread it (the compiler barrier
     // keeps the load here) rather than keep it in registers through the loop
     asm volatile("" ::: "memory");
+    Ramp ramp;
     if (live && sub == 0)
-        force_finish<R>(s, i, par, P, sp, make_recb<R>(XV[i], GQ[i], GH[i], Uc[i]), A, fin);
+        force_finish<R, kVarH>(s, i, par, sp, make_recb<R>(XV[i], GQ[i], GH[i], Uc[i]), A, fin, ramp);
+}
+
+// 16 bytes per lane from global memory straight into LDS: lane l of the wave
+// lands at dst + 16 l (dst: an LDS address, the same for the wave's lanes); a lane
+// that is switched off writes nothing.  Written as assembly because the
+// compiler waits for every such load before the next LDS read, whichever part
+// of LDS either touches.  The loads count as vector loads (lds_dma_wait), have
+// no destination register, and take their address when they issue.
+__device__ __forceinline__ void lds_dma16(const void* src, uint32_t dst) {
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
+                 :: "v"(src), "s"(__builtin_amdgcn_readfirstlane(dst)) : "memory", "m0");
+}
+// The 16 bytes after src (the instruction's offset moves both addresses).
+__device__ __forceinline__ void lds_dma16_next(const void* src, uint32_t dst) {
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off offset:16"
+                 :: "v"(src), "s"(__builtin_amdgcn_readfirstlane(dst - 16)) : "memory", "m0");
+}
+// Every vector memory access of the wave but the last N done (a builtin, so that
+// the compiler knows its own loads have arrived too).
+template <int N = 0>
+__device__ __forceinline__ void lds_dma_wait() {
+    static_assert(N < 16, "the counter's low bits");
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0x0f70 | N);   // vmcnt(N), the other counters as they are
+    asm volatile("" ::: "memory");
+}
+__device__ __forceinline__ uint32_t lds_addr(const void* p) {
+    return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void*)p;
+}
+
+// LDS image of one tile and its halo (M slots) in the staged force pass: four
+// planes of 16 bytes a slot (X, Y | Z, V0 | u_x, u_y | u_z, -), then one
+// region of records (GHRec, later GQRec, as they lie in memory: 5 units of 16
+// bytes, 3 in the mixed form, an odd number, so that the slots the lanes of a
+// 128-bit read address spread over the banks), with graded spacing the support
+// radii, and the particle of each slot.
+template <typename R>
+struct alignas(16) LdsGQ : GQRec<R> {};
+template <typename R>
+struct alignas(16) LdsGH : GHRec<R> {};
+template <typename R>
+struct LdsB {
+    static constexpr int kRec = (int)(sizeof(LdsGQ<R>) / 16);   // units of a record
+    static constexpr int kBytes = 4 * 16 + kRec * 16 + 4;       // per slot
+    static_assert(sizeof(LdsGQ<R>) == sizeof(LdsGH<R>) && kRec % 2 == 1,
+                  "records of an odd number of 16-byte units");
+    double2* xy;
+    double2* zv;
+    double2* uxy;
+    double2* uz;
+    unsigned char* rec;
+    double* hs;
+    int32_t* map;
+    __device__ LdsB(unsigned char* raw, int M, bool var_h) {
+        xy = reinterpret_cast<double2*>(raw);
+        zv = xy + M;
+        uxy = zv + M;
+        uz = uxy + M;
+        rec = reinterpret_cast<unsigned char*>(uz + M);
+        hs = reinterpret_cast<double*>(rec + (size_t)M * kRec * 16);
+        map = reinterpret_cast<int32_t*>(hs + (var_h ? M : 0));
+    }
+    __device__ LdsGH<R> gh(int m) const { return reinterpret_cast<const LdsGH<R>*>(rec)[m]; }
+    __device__ LdsGQ<R> gq(int m) const { return reinterpret_cast<const LdsGQ<R>*>(rec)[m]; }
+};
+
+// Records of slots 0 .. tot - 1 (src: GQ or GH) to dst in LDS, by consecutive
+// 16-byte units: a wave's load covers whole records, so it touches a fifth of the
+// cache lines that a load of one unit per record does.  Full waves only.
+template <int K, int kStride>
+__device__ __forceinline__ void stage_records(const void* __restrict__ src, uint32_t dst,
+                                              const int32_t* map, int tot, int wave, int n_waves,
+                                              int lane) {
+    constexpr int kU = 4;   // loads whose slots are looked up together
+    const int units = tot * K;
+    const int chunks = (units + 63) >> 6;
+    const unsigned char* __restrict__ base = static_cast<const unsigned char*>(src);
+    for (int c = wave; c < chunks; c += kU * n_waves) {
+        int32_t g[kU];
+        uint32_t f[kU];
+#pragma unroll
+        for (int q = 0; q < kU; ++q) {
+            int e = (c + q * n_waves) * 64 + lane;
+            e = e < units ? e : units - 1;
+            const uint32_t m = (uint32_t)e / K;
+            g[q] = map[m];
+            f[q] = ((uint32_t)e - m * K) * 16;
+        }
+#pragma unroll
+        for (int q = 0; q < kU; ++q) asm volatile("" : "+v"(g[q]), "+v"(f[q]));
+#pragma unroll
+        for (int q = 0; q < kU; ++q) {
+            const int cq = c + q * n_waves;
+            const unsigned char* p = base + ((uint64_t)(uint32_t)g[q] * kStride + f[q]);
+            if (cq * 64 + 64 <= units)
+                lds_dma16(p, dst + (uint32_t)cq * 1024);
+            else if (cq * 64 + lane < units)
+                lds_dma16(p, dst + (uint32_t)cq * 1024);
+        }
+    }
 }
 
 // Particle of slot m of a tile's LDS image: the tile's T particles from
-// `start`, then its halo row hl (capacity cap), which holds n (no particle)
-// for kHaloPad entries past the tile's halo count; n for slots past the
-// image.  The row entry is loaded unconditionally, at an index inside the
-// row, and blended in with masks, so that the staging's loads need neither
-// the halo count nor a branch on a loaded value (which may be turned into a
-// branch whose join waits for the load): the first round of a staging goes
-// out before the count has arrived.
+// `start`, then its halo row hl (capacity cap); n for slots past the particle
+// count.  The row entry is loaded unconditionally, at an index inside the row,
+// and blended in with masks, so that the load needs neither the halo count nor
+// a branch.
 __device__ __forceinline__ int64_t slot_particle(int m, int T, int cap, int64_t start, int64_t n,
                                                  const int32_t* __restrict__ hl) {
     const int h = m - T;
@@ -1178,17 +1428,527 @@ __device__ __forceinline__ int64_t slot_particle(int m, int T, int cap, int64_t 
 // stays at two waves per SIMD.
 __host__ __device__ constexpr int staged_block_max(int S) { return S == 4 ? 512 : kTile * S; }
 
-// LDS image of the force-pass records of one tile and its halo (M slots).
-// FP64: one 208-byte record per slot (13 units of 16 bytes, an odd number, so
-// the slots read by the lanes of one 128-bit access spread over the bank
-// groups as consecutive slots do), every field at a fixed offset from the
-// record's address.  Mixed: 128-byte records would put every slot's field at
-// the same bank group, so the image is field-major there (unit f of slot m
-// at f * M + m).
+// Waves per SIMD the two-sweep form must leave room for.
+template <int S>
+__host__ __device__ constexpr int staged_waves_min() {
+    return S >= 2 ? 3 : 1;
+}
+
+// The same pass with the tile's particles and its halo staged in LDS, in two
+// sweeps over a particle's neighbours that share one LDS image: first the
+// hourglass sums from (X, V0, u, H), then the stress sums from (X, Q, 1 - D),
+// whose records replace H's.  S lanes per particle read the image through the
+// 16-bit local neighbour slots; same arithmetic in the same order as the
+// unstaged kernel, so results are bitwise identical.  Two sweeps need 148
+// bytes of LDS per slot where one sweep's image takes 208, and fewer registers:
+// three tiles share a CU instead of two (395k particles with contact, tiles of
+// 97: 118 -> 100 us).  FP64 only: the mixed records save 12 bytes of 128.  The first sweep keeps each pair's V_j s / r in a
+// register for the second.  Graded spacing (kVarH): the slots' support radii are in
+// LDS too (one double per slot).
+template <int S, bool kVarH>
+__device__ __forceinline__ void pass_b_sweeps(const DevState& s, int par) {
+    extern __shared__ __align__(16) unsigned char lds_raw[];
+    using R = double;
+    constexpr int K = LdsB<R>::kRec, NP = kSub / S, G = kPackGroups;
+    const int M = s.lds_slots;
+    const LdsB<R> L(lds_raw, M, kVarH);
+    const int T = s.tile;
+    const int tile = __builtin_amdgcn_readfirstlane(
+        (int)work_tile(s.tile_list, s.run_count, 1, 0, gridDim.x));
+    if (tile < 0) return;
+    const int64_t start = (int64_t)tile * T;
+    const int32_t* __restrict__ hl = s.halo + (int64_t)tile * s.halo_cap;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int nw = (int)blockDim.x >> 6;   // full waves: they stage (a tile has at least one)
+    // A full wave takes 64 consecutive slots at a time; the first two rounds'
+    // row entries are loaded before the count is known.
+    const auto particle_of = [&](int m) { return slot_particle(m, T, s.halo_cap, start, s.n, hl); };
+    const int step = nw * 64;
+    int m = wave * 64 + lane;
+    int64_t g0 = particle_of(m), g1 = particle_of(m + step);
+    const int tot = T + s.halo_cnt[tile];
+    const int pl = threadIdx.x / S;
+    const int sub = threadIdx.x % S;
+    const int64_t i = start + pl;
+    const bool in = i < s.n;
+    const int64_t ii = in ? i : start;
+    const int cnt = in ? s.nnb[ii] : 0;
+    const int sp = s.spec[ii];
+    const Slots<S> slots = load_slots<S>(s.pslot, ii, sub);
+    if (wave < nw) {
+        const uint32_t l_xy = lds_addr(L.xy), l_zv = lds_addr(L.zv), l_uxy = lds_addr(L.uxy),
+                       l_uz = lds_addr(L.uz);
+        for (int b = wave * 64; b < tot; b += step, m += step) {
+            const int64_t g = g0 < s.n ? g0 : start;
+            g0 = g1;
+            if (b + 2 * step < tot) g1 = particle_of(m + 2 * step);
+            if (m < tot) {
+                L.map[m] = (int32_t)g;
+                const double2* x = reinterpret_cast<const double2*>(s.XV + g);
+                const double2* u = reinterpret_cast<const double2*>(s.U[par] + g);
+                const uint32_t at = (uint32_t)b * 16;
+                lds_dma16(x, l_xy + at);
+                lds_dma16_next(x, l_zv + at);
+                lds_dma16(u, l_uxy + at);
+                lds_dma16_next(u, l_uz + at);
+                if constexpr (kVarH) L.hs[m] = s.hs[g];
+            }
+        }
+    }
+    __syncthreads();   // the map
+    if (wave < nw)
+        stage_records<K, (int)sizeof(GQRec<R>)>(gh_of<R>(s), lds_addr(L.rec), L.map, tot, wave, nw, lane);
+    const R inv_h = R(s.specs[sp].inv_h);
+    // (neighbours past the packed slots)
+    const uint16_t* __restrict__ lp = s.lcol + s.slice_ptr[ii / kSlice] + (ii % kSlice);
+    const auto idx = [&](int k) { return (int)lp[(int64_t)(k < cnt ? k : 0) * kSlice]; };
+    lds_dma_wait();
+    __syncthreads();
+
+    const int own = in ? pl : 0;
+    const double2 xyi = L.xy[own], zvi = L.zv[own];
+    const double hsi = kVarH ? L.hs[own] : 0.0;
+    R gv[G][NP];   // V_j s / r of the packed slots' pairs
+    const auto geom = [&](int j, bool live) {
+        const double2 a = L.xy[j], b = L.zv[j];
+        return pair_geom<R, kVarH>(xyi.x, xyi.y, zvi.x, a.x, a.y, b.x, R(b.y), hsi,
+                                   kVarH ? L.hs[j] : 0.0, inv_h, live);
+    };
+    ForceAcc<R> A;
+    {
+        HgAcc<R> B[NP];
+        const double2 uxyi = L.uxy[own];
+        const double uzi = L.uz[own].x;
+        const LdsGH<R> hi = L.gh(own);
+        const auto pair = [&](int j, bool live, HgAcc<R>& acc) {
+            const PairGeom<R> p = geom(j, live);
+            const double2 a = L.uxy[j];
+            const double uz = L.uz[j].x;
+            const LdsGH<R> hj = L.gh(j);
+            hg_pair<R>(p, hj.vw, R(a.x - uxyi.x), R(a.y - uxyi.y), R(uz - uzi), hi.h, hj.h, live, acc);
+            return p.gv;
+        };
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+            if (g * kSub < cnt) {
+#pragma unroll
+                for (int t = 0; t < NP; ++t) {
+                    const bool live = g * kSub + sub + S * t < cnt;
+                    // (a bulk particle of a cubic lattice has 18 neighbours:
+                    // its fifth group is half empty)
+                    if (g < 4 || live) gv[g][t] = pair(slots.at(g, t), live, B[t]);
+                }
+            }
+        for (int k0 = G * kSub; k0 < cnt; k0 += kSub) {
+#pragma unroll
+            for (int t = 0; t < NP; ++t) {
+                const int k = k0 + sub + S * t;
+                pair(idx(k), k < cnt, B[t]);
+            }
+        }
+        A.hg = combine_partials<S>(B);
+    }
+    __syncthreads();   // every wave is done with H
+    const FinishIn fin = finish_in(s, ii, zvi.y);
+    if (wave < nw)
+        stage_records<K, (int)sizeof(GQRec<R>)>(gq_of<R>(s), lds_addr(L.rec), L.map, tot, wave, nw, lane);
+    lds_dma_wait();
+    __syncthreads();
+    {
+        StressAcc<R> B[NP];
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+            if (g * kSub < cnt) {
+#pragma unroll
+                for (int t = 0; t < NP; ++t)
+                    if (g < 4 || g * kSub + sub + S * t < cnt) {
+                        const int j = slots.at(g, t);
+                        const double2 a = L.xy[j];
+                        const double z = L.zv[j].x;
+                        const LdsGQ<R> q = L.gq(j);
+                        const R w = gv[g][t];
+                        stress_pair<R>(w * R(a.x - xyi.x), w * R(a.y - xyi.y), w * R(z - zvi.x),
+                                       q.omd, q.q, B[t]);
+                    }
+            }
+        for (int k0 = G * kSub; k0 < cnt; k0 += kSub) {
+#pragma unroll
+            for (int t = 0; t < NP; ++t) {
+                const int k = k0 + sub + S * t;
+                const int j = idx(k);
+                const PairGeom<R> p = geom(j, k < cnt);
+                const LdsGQ<R> q = L.gq(j);
+                stress_pair<R>(p.gv * p.dx, p.gv * p.dy, p.gv * p.dz, q.omd, q.q, B[t]);
+            }
+        }
+        A.st = combine_partials<S>(B);
+    }
+    if (in && sub == 0) {
+        LRecB<R> ni;
+        const double2 a = L.uxy[pl];
+        const LdsGQ<R> q = L.gq(pl);
+        ni.x = xyi.x; ni.y = xyi.y; ni.z = zvi.x;
+        ni.ux = a.x; ni.uy = a.y; ni.uz = L.uz[pl].x;
+#pragma unroll
+        for (int k = 0; k < 9; ++k) ni.q[k] = q.q[k];
+        Ramp ramp;
+        force_finish<R, kVarH>(s, i, par, sp, ni, A, fin, ramp);
+    }
+}
+
+// LDS of the pipelined force pass for a tile and its halo (M slots): the planes
+// and both regions of records of LdsB, and two maps (this tile's, the next's).
 template <typename R>
-struct LdsB;
+struct LdsP {
+    static constexpr int kRec = LdsB<R>::kRec;
+    static constexpr int kBytes = 4 * 16 + 2 * kRec * 16 + 2 * 4;
+    double2* xy;
+    double2* zv;
+    double2* uxy;
+    double2* uz;
+    LdsGH<R>* gh;
+    LdsGQ<R>* gq;
+    int32_t* map;
+    __device__ LdsP(unsigned char* raw, int M) {
+        xy = reinterpret_cast<double2*>(raw);
+        zv = xy + M;
+        uxy = zv + M;
+        uz = uxy + M;
+        gh = reinterpret_cast<LdsGH<R>*>(uz + M);
+        gq = reinterpret_cast<LdsGQ<R>*>(gh + M);
+        map = reinterpret_cast<int32_t*>(gq + M);
+    }
+};
+
+// Workgroup barrier that publishes LDS stores and waits for no vector memory.
+__device__ __forceinline__ void lds_barrier() {
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
+// stage_records a chunk (one load per lane) at a time, so that the loads can be
+// issued between pieces of arithmetic: issuing them together stalls the wave
+// for about twenty cycles each.
+template <int K, int kStride>
+struct RecordStager {
+    const unsigned char* base;
+    const int32_t* map;
+    uint32_t dst;
+    int c, n_waves, units, lane;
+    int32_t m, f;   // slot and unit within its record of the lane's unit of chunk c
+    int32_t g;      // the slot's particle
+    __device__ void start(const void* src, uint32_t dst_, const int32_t* map_, int tot, int wave,
+                          int n_waves_, int lane_) {
+        base = static_cast<const unsigned char*>(src);
+        map = map_;
+        dst = dst_;
+        units = wave < n_waves_ ? tot * K : 0;
+        c = wave * 64;
+        n_waves = n_waves_;
+        lane = lane_;
+        const uint32_t e = (uint32_t)(c + lane);
+        m = (int32_t)(e / K);
+        f = (int32_t)e - m * K;
+        g = map[c + lane < units ? m : 0];
+    }
+    __device__ void issue() {
+        if (c >= units) return;
+        const unsigned char* p = base + ((uint64_t)(uint32_t)g * kStride + (uint32_t)(f << 4));
+        if (c + 64 <= units)
+            lds_dma16(p, dst + (uint32_t)c * 16);
+        else if (c + lane < units)
+            lds_dma16(p, dst + (uint32_t)c * 16);
+        // the next chunk: 64 n_waves units on
+        c += n_waves * 64;
+        const int dm = n_waves * 64 / K, df = n_waves * 64 - dm * K;
+        f += df;
+        m += dm;
+        const int over = f >= K ? 1 : 0;
+        f -= over ? K : 0;
+        m += over;
+        if (c < units) g = map[c + lane < units ? m : 0];
+    }
+    __device__ void rest() {
+        while (c < units) issue();
+    }
+};
+
+// What a thread of the pipelined force pass holds of the next tile: loaded
+// values as they are (nothing computes with them before they have arrived:
+// vector loads return in order, so a wait for one of them would be a wait for
+// the records travelling with it).
+constexpr int kPipeRounds = 2;
+struct TileIn {
+    int32_t h[kPipeRounds];   // halo-row entries of the thread's first slots
+    int32_t halo, nnb, sp;
+};
+
+// Values computed by here: not sunk past the loads issued between the pairs,
+// which would keep every pair's inputs in registers instead.
+template <typename R>
+__device__ __forceinline__ void settle_here(R& a, R& b, R& c) {
+    asm volatile("" : "+v"(a), "+v"(b), "+v"(c));
+}
+
+// The staged force pass pipelined over a workgroup's tiles (two lanes per
+// particle, both records of the image in LDS).  One tile per workgroup spends a
+// third of its time on the latencies of its first loads, of the staging and of
+// the finish, and LDS holds too few workgroups to cover them.  Here the copies
+// into LDS run behind the arithmetic: while the first sweep (H, u: the hourglass
+// sums) runs, Q travels, and the next tile's first loads; while the second (Q:
+// the stress sums) runs, the next tile's positions, displacements, H and
+// neighbour slots, into what the first sweep is done with.  A wait is explicit,
+// once per sweep (vmcnt counts the finish's two stores too, issued last).
+// What bounds it: FP64 issue (366 us of VALU at 4.1M particles) and LDS (298 us,
+// over half of it bank conflicts of records read at random).  4.1M-particle
+// plate, FP64, tiles of 253: 717 -> 628 us; mixed 559 -> 500; Taylor bar 1M,
+// tiles of 217: 178 -> 172.
+template <typename R>
+__device__ __forceinline__ void pass_b_pipe(const DevState& s, int par) {
+    extern __shared__ __align__(16) unsigned char lds_raw[];
+    constexpr int S = 2, K = LdsP<R>::kRec, G = kPipeGroups, NP = kSub / S;
+    const int M = s.lds_slots;
+    const LdsP<R> L(lds_raw, M);
+    const int T = s.tile;
+    const int32_t n = (int32_t)s.n;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int nw = (int)blockDim.x >> 6;   // full waves: they stage (a tile has at least one)
+    const int step = nw * 64;
+    const int m0 = wave * 64 + lane;
+    const int pl = threadIdx.x / S;
+    const int sub = threadIdx.x % S;
+    const uint32_t l_xy = lds_addr(L.xy), l_zv = lds_addr(L.zv), l_uxy = lds_addr(L.uxy),
+                   l_uz = lds_addr(L.uz), l_gh = lds_addr(L.gh), l_gq = lds_addr(L.gq);
+    TileWalk walk(s.tile_list, s.run_count, (s.n + T - 1) / T);
+    int32_t tile = walk.settle(walk.load());
+    if (tile < 0) return;
+    int32_t next = walk.settle(walk.load());
+    int32_t v0 = 0;   // a per-lane zero: loads through it stay vector loads, whose
+    asm volatile("" : "+v"(v0));   // value nothing waits for until it is settled
+
+    const auto row = [&](int32_t t, int m) {   // halo-row entry of slot m, an index inside the row
+        const int h = m - T;
+        return s.halo[(int64_t)t * s.halo_cap + (h >= 0 && h < s.halo_cap ? h : 0)];
+    };
+    const auto load_first = [&](int32_t t) {
+        TileIn in;
+#pragma unroll
+        for (int q = 0; q < kPipeRounds; ++q) in.h[q] = row(t, m0 + q * step);
+        const int32_t i = t * T + pl;
+        const int32_t ii = i < n ? i : t * T;
+        in.nnb = s.nnb[ii];
+        in.sp = s.spec[ii];
+        in.halo = s.halo_cnt[t + v0];
+        return in;
+    };
+    // The particle of each slot of tile t into a map (the tile's own, then its
+    // halo; a slot past the particle count, in the last tile, takes the tile's first).
+    const auto put_map = [&](int32_t t, TileIn& in, int32_t* map) {
+        const int tot = T + in.halo;
+        const auto one = [&](int m, int32_t h) {
+            const int32_t g = m < T ? t * T + m : h;
+            return g < n ? g : t * T;
+        };
+#pragma unroll
+        for (int q = 0; q < kPipeRounds; ++q) {
+            const int m = m0 + q * step;
+            in.h[q] = one(m, in.h[q]);
+            if (wave < nw && m < tot) map[m] = in.h[q];
+        }
+        if (wave < nw)
+            for (int m = m0 + kPipeRounds * step; m < tot; m += step) map[m] = one(m, row(t, m));
+    };
+    // positions and displacements of the thread's own slots, round q of 64 per wave
+    const auto plane_round = [&](const TileIn& in, const int32_t* map, int q) {
+        const int b = wave * 64 + q * step;
+        if (wave >= nw || b + lane >= T + in.halo) return;
+        const int32_t g = q < kPipeRounds ? in.h[q] : map[b + lane];
+        const double2* x = reinterpret_cast<const double2*>(s.XV + g);
+        const double2* u = reinterpret_cast<const double2*>(s.U[par] + g);
+        const uint32_t at = (uint32_t)b * 16;
+        lds_dma16(x, l_xy + at);
+        lds_dma16_next(x, l_zv + at);
+        lds_dma16(u, l_uxy + at);
+        lds_dma16_next(u, l_uz + at);
+    };
+    const auto plane_rest = [&](const TileIn& in, const int32_t* map, int q) {
+        for (; wave * 64 + q * step < T + in.halo; ++q) plane_round(in, map, q);
+    };
+    const auto settle = [&](TileIn& in) {   // the loads have arrived
+#pragma unroll
+        for (int q = 0; q < kPipeRounds; ++q) asm volatile("" : "+v"(in.h[q]));
+        asm volatile("" : "+v"(in.nnb), "+v"(in.sp), "+v"(in.halo));
+        in.halo = __builtin_amdgcn_readfirstlane(in.halo);
+    };
+
+    RecordStager<K, (int)sizeof(GQRec<R>)> rs;
+    Ramp ramp;
+    int32_t* map = L.map;
+    TileIn cur = load_first(tile);
+    Slots<S> slots;
+    {
+        const int32_t i = tile * T + pl;
+        slots = load_slots<S>(s.pslot, i < n ? i : tile * T, sub);
+    }
+    settle(cur);
+    R inv_h = R(s.specs[cur.sp].inv_h);
+    put_map(tile, cur, map);
+    plane_rest(cur, map, 0);
+    lds_barrier();
+    rs.start(gh_of<R>(s), l_gh, map, T + cur.halo, wave, nw, lane);
+    rs.rest();
+    lds_dma_wait();
+    lds_barrier();
+    for (;;) {
+        // Sweep 1 (X, V0, u, H): hourglass sums, and V_j s X_ij / r of each pair
+        // kept for sweep 2.  This tile's Q, what its finish needs and the next
+        // tile's first loads travel meanwhile.
+        const int32_t i = tile * T + pl;
+        const bool in = i < n;
+        const int32_t ii = in ? i : tile * T;
+        const int own = in ? pl : 0;
+        const int cnt = in ? cur.nnb : 0;
+        TileIn nxt = cur;
+        if (next >= 0) nxt = load_first(next);
+        int32_t next2 = walk.load() | v0;
+        const double2 xyi = L.xy[own], zvi = L.zv[own], uxyi = L.uxy[own];
+        const double uzi = L.uz[own].x;
+        const FinishIn fin = finish_in(s, ii, zvi.y);
+        rs.start(gq_of<R>(s), l_gq, map, T + cur.halo, wave, nw, lane);
+        R gx[G * NP], gy[G * NP], gz[G * NP];
+        ForceAcc<R> A;
+        // Pair e of a lane is its partial e % NP's pair e / NP.  A bulk particle of a
+        // cubic lattice has 18 neighbours, so a lane has nine pairs: the first
+        // eight are always run (a slot past the last neighbour adds zeros), each
+        // pair's LDS reads going out ahead of the one before it; the last group's
+        // where some lane of the wave has them.
+        const auto live = [&](int e) { return (e / NP) * kSub + sub + S * (e % NP) < cnt; };
+        const auto slot = [&](int e) { return slots.at(e / NP, e % NP); };
+        constexpr int kFull = (G - 1) * NP;
+        {
+            HgAcc<R> B[NP];
+            struct Nbr {
+                double2 xy, zv, uxy;
+                double uz;
+            };
+            const LdsGH<R> hi = L.gh[own];
+            const auto load = [&](int e) {
+                const int j = slot(e);
+                return Nbr{L.xy[j], L.zv[j], L.uxy[j], L.uz[j].x};
+            };
+            const auto pair = [&](const Nbr& d, int e) {
+                const LdsGH<R> hj = L.gh[slot(e)];
+                const PairGeom<R> p = pair_geom<R, false>(xyi.x, xyi.y, zvi.x, d.xy.x, d.xy.y, d.zv.x,
+                                                          R(d.zv.y), 0.0, 0.0, inv_h, live(e));
+                gx[e] = p.gv * p.dx;
+                gy[e] = p.gv * p.dy;
+                gz[e] = p.gv * p.dz;
+                hg_pair<R>(p, hj.vw, R(d.uxy.x - uxyi.x), R(d.uxy.y - uxyi.y), R(d.uz - uzi), hi.h,
+                           hj.h, live(e), B[e % NP]);
+                settle_here(gx[e], gy[e], gz[e]);
+                settle_here(B[e % NP].g0, B[e % NP].g1, B[e % NP].g2);
+            };
+            Nbr d = load(0);
+#pragma unroll
+            for (int e = 0; e < kFull; ++e) {
+                const Nbr ahead = load(e + 1);
+                rs.issue();
+                pair(d, e);
+                d = ahead;
+            }
+            rs.rest();
+#pragma unroll
+            for (int e = kFull; e < G * NP; ++e)
+                if (__any(live(e))) {
+                    if (e > kFull) d = load(e);
+                    pair(d, e);
+                }
+            A.hg = combine_partials<S>(B);
+        }
+        lds_dma_wait();
+        int32_t* map_n = map == L.map ? L.map + M : L.map;
+        settle(nxt);
+        if (next >= 0) put_map(next, nxt, map_n);
+        next2 = walk.settle(next2);
+        lds_barrier();
+
+        // Sweep 2 (Q, 1 - D): stress sums.  The next tile's X, u, H and neighbour
+        // slots travel meanwhile (X, u and H of this one are no longer read).
+        Slots<S> slots_n = slots;
+        R inv_h_n = inv_h;
+        rs.units = 0;
+        if (next >= 0) {
+            const int32_t j = next * T + pl;
+            slots_n = load_slots<S>(s.pslot, j < n ? j : next * T, sub);
+            inv_h_n = R(s.specs[nxt.sp].inv_h);
+            rs.start(gh_of<R>(s), l_gh, map_n, T + nxt.halo, wave, nw, lane);
+        }
+        {
+            StressAcc<R> B[NP];
+            const auto load = [&](int e) { return L.gq[slot(e)]; };
+            const auto pair = [&](const LdsGQ<R>& q, int e) {
+                stress_pair<R>(gx[e], gy[e], gz[e], q.omd, q.q, B[e % NP]);
+                settle_here(B[e % NP].a0, B[e % NP].a1, B[e % NP].a2);
+                settle_here(B[e % NP].b0, B[e % NP].b1, B[e % NP].b2);
+            };
+            LdsGQ<R> q = load(0);
+#pragma unroll
+            for (int e = 0; e < kFull; ++e) {
+                const LdsGQ<R> ahead = load(e + 1);
+                if (next >= 0 && e < 2) plane_round(nxt, map_n, e);
+                if (e >= 2) rs.issue();
+                pair(q, e);
+                q = ahead;
+            }
+            if (next >= 0) {
+                plane_rest(nxt, map_n, 2);
+                rs.rest();
+            }
+#pragma unroll
+            for (int e = kFull; e < G * NP; ++e)
+                if (__any(live(e))) pair(e == kFull ? q : load(e), e);
+            A.st = combine_partials<S>(B);
+        }
+        const bool stores = in && !frozen(s, cur.sp);
+        if (stores) {
+            LRecB<R> ni;
+            const LdsGQ<R> q = L.gq[pl];
+            ni.x = xyi.x; ni.y = xyi.y; ni.z = zvi.x;
+            ni.ux = uxyi.x; ni.uy = uxyi.y; ni.uz = uzi;
+#pragma unroll
+            for (int k = 0; k < 9; ++k) ni.q[k] = q.q[k];
+            force_finish<R, false, true>(s, i, par, cur.sp, ni, A, fin, ramp, sub);
+        }
+        if (next < 0) return;
+        // the next tile's records have arrived (the finish's two stores, which
+        // follow them, need not have)
+        if (__any(stores))
+            lds_dma_wait<2>();
+        else
+            lds_dma_wait();
+#pragma unroll
+        for (int t = 0; t < NP; ++t)
+#pragma unroll
+            for (int w = 0; w < Slots<S>::W; ++w) asm volatile("" : "+v"(slots_n.w[t][w]));
+        asm volatile("" : "+v"(inv_h_n));
+        lds_barrier();
+        tile = next;
+        next = next2;
+        cur = nxt;
+        slots = slots_n;
+        inv_h = inv_h_n;
+        map = map_n;
+    }
+}
+
+// LDS image of the one-sweep form: a record of everything a pair needs per slot,
+// 208 bytes (mixed: 128; M slots).  FP64: records of 13 units of 16 bytes (an
+// odd number); mixed: a plane for each unit.
+template <typename R>
+struct LdsOne;
 template <>
-struct LdsB<double> {
+struct LdsOne<double> {
     static constexpr int kUnits = 13;   // 26 doubles
     __device__ static void put(double2* L, int, int m, const LRecB<double>& r) {
         double2* p = L + m * kUnits;
@@ -1227,7 +1987,7 @@ struct LdsB<double> {
     }
 };
 template <>
-struct LdsB<float> {
+struct LdsOne<float> {
     static constexpr int kUnits = 8;    // 6 doubles + 20 floats
     __device__ static void put(double2* L, int M, int m, const LRecB<float>& r) {
         L[0 * M + m] = double2{r.x, r.y};
@@ -1257,43 +2017,36 @@ struct LdsB<float> {
     }
 };
 
-// The same pass with the tile's particles and its halo staged in LDS: the
-// workgroup loads every record it needs once, then S lanes per particle run
-// the pair sums from LDS through the 16-bit local neighbour slots.  Same
-// arithmetic in the same order as the unstaged kernel, so results are bitwise
-// identical.  Occupancy is bounded by LDS; S lanes per particle give the
-// SIMDs several waves to switch between.
-// Waves per SIMD the staged force pass must leave room for: two workgroups per
+// Waves per SIMD the one-sweep form must leave room for: two workgroups per
 // CU need four (mixed form, two or four lanes per particle: tiles up to 196
 // and 128 particles) or three (FP64, four lanes: tiles up to 96).  With graded
 // spacing the mixed form needs more than 128 registers: three.
 template <typename R, int S, bool kVarH = false>
-__host__ __device__ constexpr int staged_waves_min() {
+__host__ __device__ constexpr int one_sweep_waves_min() {
     return sizeof(R) == 4 && S >= 2 ? (kVarH ? 3 : 4) : (S == 4 ? 3 : 1);
 }
 // Whether the finish's inputs are loaded before the staging (their registers
 // then live through the pair sums; the mixed form with two lanes has none to
 // spare within its 128).
 template <typename R, int S>
-__host__ __device__ constexpr bool staged_finish_early() {
+__host__ __device__ constexpr bool one_sweep_finish_early() {
     return !(sizeof(R) == 4 && S == 2);
 }
 
-// Neighbour-index groups the staged force pass loads before its staging.
-template <typename R, int S>
-__host__ __device__ constexpr int staged_pre_groups() {
-    return S == 1 ? 1 : sizeof(R) == 8 ? (S == 2 ? 6 : 2) : S == 2 ? 4 : 1;
-}
-
-// Graded spacing (kVarH): the slots' support radii follow the records in LDS
-// (one double per slot).
+// The staged force pass in one sweep over an image of whole records, staged
+// through registers, a workgroup per tile: a chain of few latencies, which is
+// what bounds it where tiles are few (25k particles FP64, tiles of 98: 12.3 us,
+// 12.8 with a load for each neighbour slot and the groups' records by lane).  Graded spacing (kVarH): the slots'
+// support radii follow the records in LDS (one double per slot).
 template <typename R, int S, bool kVarH = false>
 __global__ void __launch_bounds__(staged_block_max(S))
-__attribute__((amdgpu_waves_per_eu(staged_waves_min<R, S, kVarH>(), 8))) k_pass_b_staged(DevState s, int par) {
+__attribute__((amdgpu_waves_per_eu(one_sweep_waves_min<R, S, kVarH>(), 8)))
+k_pass_b_one(DevState s, int par) {
     extern __shared__ __align__(16) unsigned char lds_raw[];
+    constexpr int NP = kSub / S, G = kPackGroups;
     double2* __restrict__ L = reinterpret_cast<double2*>(lds_raw);
     const int M = s.lds_slots;
-    double* __restrict__ Lhs = reinterpret_cast<double*>(L + (size_t)M * LdsB<R>::kUnits);
+    double* __restrict__ Lhs = reinterpret_cast<double*>(L + (size_t)M * LdsOne<R>::kUnits);
     const int T = s.tile;
     const int B = T * S;
     const int64_t tile = work_tile(s.tile_list, s.run_count, 1, 0, gridDim.x);
@@ -1307,7 +2060,7 @@ __attribute__((amdgpu_waves_per_eu(staged_waves_min<R, S, kVarH>(), 8))) k_pass_
     // Two slots per thread per round, their index loads issued before their
     // record loads and those before the LDS stores.  The first round's halo
     // indices are loaded before anything else; the particle's own scalars, its
-    // first neighbour slots and what its finish needs follow, so that their
+    // neighbour slots and what its finish needs follow, so that their
     // latencies overlap those of the staging.  The first round needs no halo
     // count (slots past the image hold n): FP64 reads the count after it (two
     // memory latencies before the barrier); the mixed form reads it first.
@@ -1321,18 +2074,13 @@ __attribute__((amdgpu_waves_per_eu(staged_waves_min<R, S, kVarH>(), 8))) k_pass_
     const int64_t i = start + pl;
     const bool in = i < s.n;
     const int64_t ii = in ? i : start;
-    // (the loads that others depend on first: count, slice start, specimen)
     const int cnt = in ? s.nnb[i] : 0;
-    const int64_t slice0 = s.slice_ptr[ii / kSlice];
     const int sp = s.spec[ii];
-    const DevSpec& P = s.specs[sp];
-    const R inv_h = R(P.inv_h);
-    const uint16_t* __restrict__ lp = s.lcol + slice0 + (ii % kSlice);
-    const auto idx = [&](int k) { return (int)lp[(int64_t)k * kSlice]; };
-    const auto first = first_indices<S, staged_pre_groups<R, S>(), true>(cnt, sub, idx);
-    constexpr bool kEarly = staged_finish_early<R, S>();
+    const Slots<S> slots = load_slots<S>(s.pslot, ii, sub);
+    const R inv_h = R(s.specs[sp].inv_h);
+    constexpr bool kEarly = one_sweep_finish_early<R, S>();
     FinishIn fin_early;
-    if constexpr (kEarly) fin_early = finish_in<kVarH>(s, ii, P);
+    if constexpr (kEarly) fin_early = finish_in(s, ii, XV[ii].w);
     const auto stage = [&](int m0, int64_t g0, int64_t g1) {
         const int64_t l0 = g0 < s.n ? g0 : start, l1 = g1 < s.n ? g1 : start;
         const LRecB<R> r0 = make_recb<R>(XV[l0], GQ[l0], GH[l0], Uc[l0]);
@@ -1343,11 +2091,11 @@ __attribute__((amdgpu_waves_per_eu(staged_waves_min<R, S, kVarH>(), 8))) k_pass_
             h1 = s.hs[l1];
         }
         if (g0 < s.n) {
-            LdsB<R>::put(L, M, m0, r0);
+            LdsOne<R>::put(L, M, m0, r0);
             if constexpr (kVarH) Lhs[m0] = h0;
         }
         if (g1 < s.n) {
-            LdsB<R>::put(L, M, m0 + B, r1);
+            LdsOne<R>::put(L, M, m0 + B, r1);
             if constexpr (kVarH) Lhs[m0 + B] = h1;
         }
     };
@@ -1356,8 +2104,6 @@ __attribute__((amdgpu_waves_per_eu(staged_waves_min<R, S, kVarH>(), 8))) k_pass_
         const int tot = T + s.halo_cnt[tile];
         for (m0 += 2 * B; m0 < tot; m0 += 2 * B) stage(m0, particle_of(m0), particle_of(m0 + B));
     } else {
-        // (the mixed form: a plain loop, whose registers fit four waves per
-        // SIMD with the preloaded slots)
         const int tot = T + s.halo_cnt[tile];
         for (; m0 < tot; m0 += 2 * B) {
             stage(m0, g0, g1);
@@ -1367,20 +2113,72 @@ __attribute__((amdgpu_waves_per_eu(staged_waves_min<R, S, kVarH>(), 8))) k_pass_
     }
     __syncthreads();
     const auto rec = [&](int m) {
-        LRecB<R> r = LdsB<R>::get(L, M, m);
+        LRecB<R> r = LdsOne<R>::get(L, M, m);
         if constexpr (kVarH) r.hs = Lhs[m];
         return r;
     };
-    const LRecB<R> ni = rec(in ? pl : 0);
-    const ForceAcc<R> A = pair_sums<R, S, kVarH>(ni, cnt, sub, inv_h, idx, rec, first);
-    // the particle's own Q is needed only now: reread it rather than keep it
-    // in registers through the pair loop (the image is not written after the
+    ForceAcc<R> A;
+    {
+        const LRecB<R> ni = rec(in ? pl : 0);
+        ForceAcc<R> P[NP];
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+            if (g * kSub < cnt) {
+#pragma unroll
+                for (int t = 0; t < NP; ++t)
+                    force_pair<R, kVarH>(ni, rec(slots.at(g, t)), inv_h, P[t],
+                                         g * kSub + sub + S * t < cnt);
+            }
+        if (G * kSub < cnt) {   // neighbours past the packed slots, loaded one group ahead
+            const uint16_t* __restrict__ lp = s.lcol + s.slice_ptr[ii / kSlice] + (ii % kSlice);
+            int q[NP];
+#pragma unroll
+            for (int t = 0; t < NP; ++t) {
+                const int k = G * kSub + sub + S * t;
+                q[t] = lp[(int64_t)(k < cnt ? k : 0) * kSlice];
+            }
+            for (int k0 = G * kSub; k0 < cnt; k0 += kSub) {
+                int cur[NP];
+#pragma unroll
+                for (int t = 0; t < NP; ++t) {
+                    cur[t] = q[t];
+                    const int kn = k0 + kSub + sub + S * t;
+                    q[t] = lp[(int64_t)(kn < cnt ? kn : 0) * kSlice];
+                }
+#pragma unroll
+                for (int t = 0; t < NP; ++t)
+                    force_pair<R, kVarH>(ni, rec(cur[t]), inv_h, P[t], k0 + sub + S * t < cnt);
+            }
+        }
+        A = combine_partials<S>(P);
+    }
+    // the particle's own record is needed only now: reread it rather than keep
+    // it in registers through the pair loop (the image is not written after the
     // barrier above, so a compiler barrier suffices: waves go on to their
     // finish as their own sums end)
     asm volatile("" ::: "memory");
-    if (in && sub == 0 && !frozen(s, sp))
-        force_finish<R>(s, i, par, P, sp, LdsB<R>::get(L, M, pl), A,
-                        kEarly ? fin_early : finish_in<kVarH>(s, i, P));
+    Ramp ramp;
+    if (in && sub == 0)
+        force_finish<R, kVarH>(s, i, par, sp, LdsOne<R>::get(L, M, pl), A,
+                               kEarly ? fin_early : finish_in(s, ii, XV[ii].w), ramp);
+}
+
+// The same in the forms that stage by asynchronous copies: pipelined with two
+// lanes per particle and one support for all, else (FP64) in two sweeps.
+template <typename R, int S, bool kVarH = false>
+__global__ void __launch_bounds__(staged_block_max(S))
+__attribute__((amdgpu_waves_per_eu((!kVarH && S == 2) ? 2 : staged_waves_min<S>(), 8)))
+k_pass_b_staged(DevState s, int par) {
+    if constexpr (!kVarH && S == 2)
+        pass_b_pipe<R>(s, par);
+    else
+        pass_b_sweeps<S, kVarH>(s, par);
+}
+
+// Two sweeps with two lanes per particle.
+__global__ void __launch_bounds__(staged_block_max(2))
+__attribute__((amdgpu_waves_per_eu(staged_waves_min<2>(), 8))) k_pass_b_wide(DevState s, int par) {
+    pass_b_sweeps<2, false>(s, par);
 }
 
 // Pass A (deformation and constitutive update to t^{n+1}).
@@ -1567,11 +2365,12 @@ __device__ __forceinline__ void pass_a_update(const DevState& s, int64_t i, int 
     mm33(M, in.Li, Fd);
     GQRec<R>* __restrict__ GQ = gq_of<R>(s);
     GHRec<R>* __restrict__ GH = gh_of<R>(s);
-    R Hn[9], sn[6];
+    R Hn[9], sn[6], vw;
     {
         const GHRec<R> gi = GH[i];
 #pragma unroll
         for (int k = 0; k < 9; ++k) Hn[k] = gi.h[k];
+        vw = gi.vw;
     }
     if constexpr (std::is_same<R, float>::value) {
 #pragma unroll
@@ -1623,7 +2422,8 @@ __device__ __forceinline__ void pass_a_update(const DevState& s, int64_t i, int 
 #pragma unroll
     for (int k = 0; k < 9; ++k) ho.h[k] = o.H[k];
     go.omd = R(1.0 - o.D);
-    ho.pad = R(0);
+    // V0 (1 - D) for the force pass: kept with H, and unless D changed as it was
+    ho.vw = o.D != Di ? R(s.XV[is].w) * go.omd : vw;
     GQ[is] = go;
     GH[is] = ho;
     // The plastic strain and its accumulators change only where the particle
@@ -1841,16 +2641,33 @@ template <int S>
 static hipError_t launch_b(const DevState& s, int parity, int block, bool mixed, hipStream_t st,
                            size_t lds_bytes) {
     if (s.staged) {
-        const unsigned grid = (unsigned)((s.n + s.tile - 1) / s.tile);
-        if (s.var_h) {   // graded spacing: per-pair supports
+        const unsigned grid = (unsigned)s.grid_b;
+        const int threads = s.tile * S;
+        if (s.form_b == kFormOne) {
+            if (s.var_h) {   // graded spacing: per-pair supports
+                if (mixed)
+                    k_pass_b_one<float, S, true><<<grid, threads, lds_bytes, st>>>(s, parity);
+                else
+                    k_pass_b_one<double, S, true><<<grid, threads, lds_bytes, st>>>(s, parity);
+            } else if (mixed) {
+                k_pass_b_one<float, S><<<grid, threads, lds_bytes, st>>>(s, parity);
+            } else {
+                k_pass_b_one<double, S><<<grid, threads, lds_bytes, st>>>(s, parity);
+            }
+        } else if (s.form_b == kFormPipe) {
+            if (S != 2 || s.var_h) return hipErrorInvalidValue;
             if (mixed)
-                k_pass_b_staged<float, S, true><<<grid, s.tile * S, lds_bytes, st>>>(s, parity);
+                k_pass_b_staged<float, 2><<<grid, threads, lds_bytes, st>>>(s, parity);
             else
-                k_pass_b_staged<double, S, true><<<grid, s.tile * S, lds_bytes, st>>>(s, parity);
-        } else if (mixed) {
-            k_pass_b_staged<float, S><<<grid, s.tile * S, lds_bytes, st>>>(s, parity);
+                k_pass_b_staged<double, 2><<<grid, threads, lds_bytes, st>>>(s, parity);
         } else {
-            k_pass_b_staged<double, S><<<grid, s.tile * S, lds_bytes, st>>>(s, parity);
+            if (mixed) return hipErrorInvalidValue;
+            if (s.var_h)
+                k_pass_b_staged<double, S, true><<<grid, threads, lds_bytes, st>>>(s, parity);
+            else if constexpr (S == 2)
+                k_pass_b_wide<<<grid, threads, lds_bytes, st>>>(s, parity);
+            else
+                k_pass_b_staged<double, S><<<grid, threads, lds_bytes, st>>>(s, parity);
         }
         return hipGetLastError();
     }
@@ -1882,26 +2699,51 @@ hipError_t launch_pass_b(const DevState& s, int parity, int block, int sub, bool
 
 int staged_tile_max(int sub) { return staged_block_max(sub) / sub; }
 
-size_t staged_record_bytes(bool mixed, bool var_h) {
-    return 16 * (size_t)(mixed ? LdsB<float>::kUnits : LdsB<double>::kUnits) + (var_h ? 8 : 0);
+size_t staged_one_bytes(bool mixed, bool var_h) {
+    return (size_t)(mixed ? LdsOne<float>::kUnits : LdsOne<double>::kUnits) * 16 + (var_h ? 8 : 0);
+}
+
+size_t staged_sweep_bytes(bool var_h) { return LdsB<double>::kBytes + (var_h ? 8 : 0); }
+
+size_t staged_pipe_bytes(bool mixed) {
+    return (size_t)(mixed ? LdsP<float>::kBytes : LdsP<double>::kBytes);
+}
+
+int staged_pipe_neighbours() { return kSub * kPipeGroups; }
+
+// Workgroups of the pipelined force pass (threads and LDS bytes each) that
+// share a CU.
+hipError_t staged_blocks_per_cu(bool mixed, int threads, size_t lds_bytes, int* out) {
+    const void* f = mixed ? reinterpret_cast<const void*>(&k_pass_b_staged<float, 2>)
+                          : reinterpret_cast<const void*>(&k_pass_b_staged<double, 2>);
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(out, f, threads, lds_bytes);
 }
 
 size_t staged_a_record_bytes(bool var_h) { return kLdsABytes + (var_h ? 8 : 0); }
 
 // Dynamic LDS above the default limit must be allowed per kernel.
 hipError_t prepare_staged(size_t lds_bytes_b) {
-    const void* fns[12] = {reinterpret_cast<const void*>(&k_pass_b_staged<double, 1>),
-                           reinterpret_cast<const void*>(&k_pass_b_staged<float, 1>),
-                           reinterpret_cast<const void*>(&k_pass_b_staged<double, 2>),
-                           reinterpret_cast<const void*>(&k_pass_b_staged<float, 2>),
-                           reinterpret_cast<const void*>(&k_pass_b_staged<double, 4>),
-                           reinterpret_cast<const void*>(&k_pass_b_staged<float, 4>),
-                           reinterpret_cast<const void*>(&k_pass_b_staged<double, 1, true>),
-                           reinterpret_cast<const void*>(&k_pass_b_staged<float, 1, true>),
-                           reinterpret_cast<const void*>(&k_pass_b_staged<double, 2, true>),
-                           reinterpret_cast<const void*>(&k_pass_b_staged<float, 2, true>),
-                           reinterpret_cast<const void*>(&k_pass_b_staged<double, 4, true>),
-                           reinterpret_cast<const void*>(&k_pass_b_staged<float, 4, true>)};
+    const void* const fns[] = {
+        reinterpret_cast<const void*>(&k_pass_b_wide),
+        reinterpret_cast<const void*>(&k_pass_b_staged<double, 1>),
+        reinterpret_cast<const void*>(&k_pass_b_staged<double, 2>),
+        reinterpret_cast<const void*>(&k_pass_b_staged<float, 2>),
+        reinterpret_cast<const void*>(&k_pass_b_staged<double, 4>),
+        reinterpret_cast<const void*>(&k_pass_b_staged<double, 1, true>),
+        reinterpret_cast<const void*>(&k_pass_b_staged<double, 2, true>),
+        reinterpret_cast<const void*>(&k_pass_b_staged<double, 4, true>),
+        reinterpret_cast<const void*>(&k_pass_b_one<double, 1>),
+        reinterpret_cast<const void*>(&k_pass_b_one<float, 1>),
+        reinterpret_cast<const void*>(&k_pass_b_one<double, 2>),
+        reinterpret_cast<const void*>(&k_pass_b_one<float, 2>),
+        reinterpret_cast<const void*>(&k_pass_b_one<double, 4>),
+        reinterpret_cast<const void*>(&k_pass_b_one<float, 4>),
+        reinterpret_cast<const void*>(&k_pass_b_one<double, 1, true>),
+        reinterpret_cast<const void*>(&k_pass_b_one<float, 1, true>),
+        reinterpret_cast<const void*>(&k_pass_b_one<double, 2, true>),
+        reinterpret_cast<const void*>(&k_pass_b_one<float, 2, true>),
+        reinterpret_cast<const void*>(&k_pass_b_one<double, 4, true>),
+        reinterpret_cast<const void*>(&k_pass_b_one<float, 4, true>)};
     for (const void* f : fns) {
         hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize,
                                            (int)lds_bytes_b);
@@ -1978,19 +2820,20 @@ struct FieldRef {
 
 __device__ __forceinline__ FieldRef field_ref(const DevState& s, int field, int par) {
     const int64_t np = s.np;
+    constexpr int64_t kRec32 = sizeof(GQRec<float>) / 4;
     switch (field) {
         case F_X: return {reinterpret_cast<const double*>(s.XV), nullptr, 3, 0, 1, 4};
         case F_U: return {reinterpret_cast<const double*>(s.U[par]), nullptr, 3, 0, 1, 4};
         case F_V: return {reinterpret_cast<const double*>(s.VW), nullptr, 3, 0, 1, 4};
         case F_DEFGRAD:
             return s.GH ? FieldRef{reinterpret_cast<const double*>(s.GH), nullptr, 9, 1, 1, 10}
-                        : FieldRef{nullptr, reinterpret_cast<const float*>(s.GH32), 9, 1, 1, 10};
+                        : FieldRef{nullptr, reinterpret_cast<const float*>(s.GH32), 9, 1, 1, kRec32};
         case F_H:   // F - I as stored, without the round trip through F
             return s.GH ? FieldRef{reinterpret_cast<const double*>(s.GH), nullptr, 9, 0, 1, 10}
-                        : FieldRef{nullptr, reinterpret_cast<const float*>(s.GH32), 9, 0, 1, 10};
+                        : FieldRef{nullptr, reinterpret_cast<const float*>(s.GH32), 9, 0, 1, kRec32};
         case F_Q:
             return s.GQ ? FieldRef{reinterpret_cast<const double*>(s.GQ), nullptr, 9, 0, 1, 10}
-                        : FieldRef{nullptr, reinterpret_cast<const float*>(s.GQ32), 9, 0, 1, 10};
+                        : FieldRef{nullptr, reinterpret_cast<const float*>(s.GQ32), 9, 0, 1, kRec32};
         case F_SIGMA:
             return s.sig ? FieldRef{s.sig, nullptr, 6, 0, np, 1} : FieldRef{nullptr, s.sig32, 6, 0, np, 1};
         case F_EPS_P: return {s.eps_p, nullptr, 1, 0, np, 1};
@@ -2020,8 +2863,8 @@ __global__ void k_get(DevState s, int field, int par, double* __restrict__ dst) 
     }
 }
 
-// Writes keep the gathered copies consistent: damage also sets 1 - D in the
-// force-pass record and V0 (1 - D) in the velocity record.
+// Writes keep the gathered copies consistent: damage also sets 1 - D and V0 (1
+// - D) in the force-pass records and V0 (1 - D) in the velocity record.
 __global__ void k_set(DevState s, int field, int par, const double* __restrict__ src) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= s.n) return;
@@ -2038,7 +2881,13 @@ __global__ void k_set(DevState s, int field, int par, const double* __restrict__
     }
     if (r.kind == 2) {
         const double D = src[i];
-        if (s.GQ) s.GQ[p].omd = 1.0 - D; else s.GQ32[p].omd = (float)(1.0 - D);
+        if (s.GQ) {
+            s.GQ[p].omd = 1.0 - D;
+            s.GH[p].vw = s.XV[p].w * s.GQ[p].omd;
+        } else {
+            s.GQ32[p].omd = (float)(1.0 - D);
+            s.GH32[p].vw = float(s.XV[p].w) * s.GQ32[p].omd;
+        }
         s.VW[p].w = s.XV[p].w * (1.0 - D);
     }
 }

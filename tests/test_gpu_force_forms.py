@@ -1,0 +1,79 @@
+"""The staged force pass's forms (one sweep, two sweeps, pipelined) against the
+unstaged kernel, which the parity tests compare with the oracle: the same
+arithmetic in the same order, so bitwise, at tiles whose edges fall inside
+and on waves, with a ragged last tile, more neighbours than the packed slots or
+the pipelined form hold, failed particles, contact between two specimens, and
+a specimen that run control has stopped."""
+import numpy as np
+import pytest
+
+from paper_1901_07374_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+KEYS = ("force", "v", "u", "F", "Q", "sig", "D")
+# LDS bytes per slot of each form (FP64, mixed)
+BYTES = {"one": (208, 128), "two": (148, None), "pipe": (232, 168)}
+
+
+@pytest.fixture(scope="module")
+def tl():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1901_07374_amd import tlsph
+    return tlsph
+
+
+def wide(dx):
+    """Support of 1.8 dx: 26 neighbours, more than the packed slots hold."""
+    return I.notched_bar(dx=dx, h=1.8 * dx)
+
+
+PROBLEMS = {
+    "bar": lambda: I.notched_bar(dx=0.27e-3),
+    "bar_large": lambda: I.notched_bar(dx=0.2e-3),
+    "wide": lambda: wide(0.5e-3),
+    "wide_large": lambda: wide(0.27e-3),
+    "contact_av": lambda: I.with_materials(I.bar_collision(dx=0.13e-3, gap=0.0), **I.DAMPING),
+    "stopped": lambda: I.bar_batch(n_spec=3, counts=(70000, 50000, 60000)),
+}
+# problem, precision, lanes, tile, the form it takes
+CASES = [
+    ("bar", "fp64", 2, 160, "pipe"), ("bar", "fp64", 2, 163, "pipe"),
+    ("bar", "fp64", 2, 66, "two"), ("bar", "fp64", 4, 65, "two"), ("bar", "fp64", 1, 66, "two"),
+    ("bar", "fp64", 2, 96, "one"), ("bar", "fp64", 1, 100, "one"),
+    ("bar_large", "mixed", 2, 96, "pipe"), ("bar_large", "mixed", 2, 195, "pipe"),
+    ("bar", "mixed", 2, 128, "one"), ("bar", "mixed", 4, 100, "one"),
+    ("wide", "fp64", 2, 66, "one"), ("wide", "mixed", 2, 66, "one"),
+    ("wide_large", "fp64", 2, 67, "two"), ("wide_large", "fp64", 4, 64, "two"),
+    ("contact_av", "fp64", 2, 192, "pipe"), ("stopped", "fp64", 2, 161, "pipe"),
+]
+
+
+@pytest.mark.parametrize("problem,precision,lanes,tile,form", CASES)
+def test_forms_are_bitwise_the_unstaged_pass(tl, problem, precision, lanes, tile, form):
+    p = PROBLEMS[problem]()
+    st = I.random_state(p, seed=11, v_scale=1.0, u_scale=1e-7)
+    outs = []
+    for shape in ((False, 4, 256, 256, 0), (True, lanes, 256, 256, tile)):
+        g = tl.Sim(p, precision=tl.FP64 if precision == "fp64" else tl.MIXED,
+                   flags=tl.STORE_FORCE, k_cap=32)
+        g.set_launch_shape(*shape)
+        g.set_state(st)
+        if problem == "stopped":
+            g.set_run_control([{"group": 2 * q + 1, "axis": 2, "sign": -1.0, "drop": 0.5,
+                                "min_peak": 1e12, "step_cap": 2 if q == 1 else 0}
+                               for q in range(p.n_spec)])
+            g.run(4, check_every=1)
+            assert g.run_status()["steps"][1] == 2
+        else:
+            g.step(3)
+        outs.append({k: g.get(k) for k in KEYS})
+        inf = g.info()
+    print(problem, precision, lanes, tile, p.n, inf, flush=True)
+    assert inf["staged"] and inf["tile"] == tile and inf["lanes_per_particle"] == lanes
+    per_slot = BYTES[form][precision == "mixed"]
+    assert inf["lds_bytes"] % per_slot == 0 and inf["lds_bytes"] > tile * per_slot
+    for k in KEYS:
+        assert np.array_equal(outs[0][k], outs[1][k]), k
