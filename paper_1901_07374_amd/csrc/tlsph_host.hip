@@ -758,7 +758,8 @@ tlsph_status tlsph_build_neighbors(tlsph_ctx* c, const double* X, const double* 
         (void)hipGraphExecDestroy(c->gexec);
         c->gexec = nullptr;
     }
-    // error words: first singular = INT_MAX, max count = 0, flags = 0, build = 0
+    // error words: first singular = INT_MAX, max count = 0, flags = 0, build = 0, largest
+    // halo = 0, members of groups = 0, and 64 bits: the pairs = 0
     const int32_t init_err[8] = {0x7fffffff, 0, 0, 0, 0, 0, 0, 0};
     HIPCHK(c, hipMemcpyAsync(c->ws + L.err, init_err, sizeof init_err, hipMemcpyHostToDevice, stream));
     BuildBuffers b{};
@@ -770,8 +771,13 @@ tlsph_status tlsph_build_neighbors(tlsph_ctx* c, const double* X, const double* 
     b.keys = at<uint64_t>(c, L.keys);
     b.vals = at<int32_t>(c, L.vals);
     b.n_pow2 = L.n_pow2;
+    b.cell = at<CSlot>(c, L.hslot);
+    b.H = 2 * L.n_pow2;
+    b.found = at<int32_t>(c, L.halo);
+    b.k_cap = L.k_cap;
+    b.part = at<int64_t>(c, L.diag_part);
     HIPCHK(c, launch_build_count(c->st, b, stream));
-    int32_t err[8];
+    alignas(8) int32_t err[8];
     int64_t total_slots = 0;
     HIPCHK(c, hipMemcpyAsync(err, c->ws + L.err, sizeof err, hipMemcpyDeviceToHost, stream));
     HIPCHK(c, hipMemcpyAsync(&total_slots, c->ws + L.slice_ptr + L.n_slices * 8, 8,
@@ -782,6 +788,9 @@ tlsph_status tlsph_build_neighbors(tlsph_ctx* c, const double* X, const double* 
     if (err[1] > L.k_cap || total_slots > (int64_t)L.k_cap * L.np)
         return fail(c, TLSPH_E_CAPACITY, "a particle has " + std::to_string(err[1]) +
                                              " neighbours, k_cap is " + std::to_string(L.k_cap));
+    int64_t pairs;   // neighbour pairs: sum of counts
+    memcpy(&pairs, &err[6], 8);
+    const int64_t members = err[5];   // particles with a prescribed-velocity group
     HIPCHK(c, launch_build_fill(c->st, b, stream));
     c->st.staged = 0;
     c->staged_ok = false;
@@ -809,7 +818,7 @@ tlsph_status tlsph_build_neighbors(tlsph_ctx* c, const double* X, const double* 
         c->tile_auto = (int)(T < 64 ? 64 : (T > kTile ? kTile : T));
     }
     HIPCHK(c, launch_shape_and_init(c->st, L.mixed, stream));
-    HIPCHK(c, launch_bc_lists(c->st, b.keys, b.vals, L.n_pow2, at<int32_t>(c, L.bc_list),
+    HIPCHK(c, launch_bc_lists(c->st, b.keys, b.vals, members, at<int32_t>(c, L.bc_list),
                               at<int64_t>(c, L.bc_ptr), stream));
     HIPCHK(c, hipMemcpyAsync(err, c->ws + L.err, sizeof err, hipMemcpyDeviceToHost, stream));
     HIPCHK(c, hipStreamSynchronize(stream));
@@ -830,14 +839,13 @@ tlsph_status tlsph_build_neighbors(tlsph_ctx* c, const double* X, const double* 
             c->block_b = c->st.tile * c->sub_b;
         }
     }
-    // group sizes and neighbour counts to the host (one synchronisation)
+    // group sizes to the host
     std::vector<int64_t> bptr((size_t)L.n_bc + 1, 0);
-    std::vector<int32_t> cnt(L.np);
-    if (L.n_bc > 0)
+    if (L.n_bc > 0) {
         HIPCHK(c, hipMemcpyAsync(bptr.data(), c->ws + L.bc_ptr, bptr.size() * 8,
                                  hipMemcpyDeviceToHost, stream));
-    HIPCHK(c, hipMemcpyAsync(cnt.data(), c->ws + L.nnb, L.np * 4, hipMemcpyDeviceToHost, stream));
-    HIPCHK(c, hipStreamSynchronize(stream));
+        HIPCHK(c, hipStreamSynchronize(stream));
+    }
     // diagnostics segments: chunks of each specimen, then of each group
     {
         std::vector<int64_t>& seg = c->diag_seg_host;
@@ -855,10 +863,7 @@ tlsph_status tlsph_build_neighbors(tlsph_ctx* c, const double* X, const double* 
         c->diag_chunks_spec = seg[L.n_spec];
         c->diag_chunks_all = seg.back();
     }
-    // neighbour pairs: sum of counts
-    int64_t nnz = 0;
-    for (int64_t p = 0; p < L.n; ++p) nnz += cnt[p];
-    c->nnz = nnz;
+    c->nnz = pairs;
     c->slots = total_slots;
     c->built = true;
     if (c->st.contact) {   // a valid list before any force pass (autotune included)
@@ -1072,7 +1077,7 @@ tlsph_status tlsph_neighbor_count(const tlsph_ctx* c, int64_t* nnz) {
 tlsph_status tlsph_get_neighbors(tlsph_ctx* c, int64_t* row_ptr, int32_t* col, hipStream_t stream) {
     if (!c || !row_ptr || !col) return fail(c, TLSPH_E_INVALID_ARG, "null argument");
     if (!c->built) return fail(c, TLSPH_E_BAD_STATE, "get_neighbors before build");
-    HIPCHK(c, launch_export_neighbors(c->st, row_ptr, col, nullptr, stream));
+    HIPCHK(c, launch_export_neighbors(c->st, row_ptr, col, at<int64_t>(c, c->L.diag_part), stream));
     return TLSPH_OK;
 }
 

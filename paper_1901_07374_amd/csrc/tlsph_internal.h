@@ -224,6 +224,13 @@ hipError_t launch_pass_b(const DevState& s, int parity, int block, int sub, bool
                          hipStream_t st, size_t lds_bytes = 0);
 hipError_t launch_pass_a(const DevState& s, int parity, int block, bool mixed, hipStream_t st);
 
+// Slot of a cell hash: the contact search's (below), and the table of occupied
+// cells while the neighbour lists are built.
+struct CSlot {
+    uint64_t key;
+    int32_t cnt;
+    int32_t start;
+};
 struct BuildBuffers {
     const double* X_in;      // caller order [3][n]
     const double* V0_in;
@@ -233,6 +240,11 @@ struct BuildBuffers {
     uint64_t* keys;          // [n_pow2]
     int32_t* vals;           // [n_pow2]
     int64_t n_pow2;
+    CSlot* cell;             // [H] the cells' table (the contact search's, free until it runs)
+    int64_t H;
+    int32_t* found;          // [k_cap][n] neighbour lists before they are sliced (the halo lists' place)
+    int32_t k_cap;
+    int64_t* part;           // block sums of the scan
 };
 
 hipError_t launch_build_count(DevState& s, const BuildBuffers& b, hipStream_t st);
@@ -283,11 +295,6 @@ hipError_t launch_diagnostics(const DevState& s, int parity, const int32_t* bc_l
 // index order, with their current positions and contact radii, and their
 // reference positions and support radii, beside them.
 constexpr int kCHashScanB = 4096;
-struct CSlot {
-    uint64_t key;
-    int32_t cnt;
-    int32_t start;
-};
 struct CHash {
     CSlot* slot;      // [H]
     int32_t* boff;    // [H / kCHashScanB + 1]
@@ -307,7 +314,7 @@ hipError_t launch_contact_build(const DevState& s, int parity, uint64_t* keys, i
 hipError_t launch_run_control(const DevState& s, int parity, RunSpec* run, const int32_t* bc_list,
                               const int64_t* bc_ptr, hipStream_t st);
 hipError_t launch_tile_list(const DevState& s, int force, hipStream_t st);
-hipError_t launch_bc_lists(const DevState& s, uint64_t* keys, int32_t* vals, int64_t n_pow2,
+hipError_t launch_bc_lists(const DevState& s, uint64_t* keys, int32_t* vals, int64_t m,
                            int32_t* bc_list, int64_t* bc_ptr, hipStream_t st);
 
 }  // namespace tlsph

@@ -63,14 +63,32 @@ __device__ __forceinline__ uint64_t cell_key(uint32_t x, uint32_t y, uint32_t z)
 // specimen's h, or with graded spacing the largest support h_per_spacing
 // (max V0)^(1/3), each a hair larger so that pairs closer than the support
 // never sit two cells apart after rounding.
+// Found by all compute units: chunks of a specimen reduce in LDS and meet in
+// atomics on the extrema as ordered integers, kept in the record itself (one
+// workgroup per specimen took 281 us for 200k particles, now 11).
 constexpr int kBBox = 8;
-__global__ void k_bbox(const double* __restrict__ X, const double* __restrict__ V0, int64_t n,
-                       const int64_t* __restrict__ off, const DevSpec* __restrict__ specs,
-                       double* __restrict__ bbox) {
+constexpr int kBBoxChunk = 2048;   // particles per workgroup, at least
+__device__ __forceinline__ unsigned long long ordered_bits(double x) {
+    const unsigned long long b = (unsigned long long)__double_as_longlong(x);
+    return b ^ ((b >> 63) ? ~0ull : 1ull << 63);
+}
+__device__ __forceinline__ double from_ordered_bits(unsigned long long b) {
+    return __longlong_as_double((long long)(b ^ ((b >> 63) ? 1ull << 63 : ~0ull)));
+}
+__global__ void k_bbox_clear(unsigned long long* __restrict__ bits, int n_spec) {
+    const int t = blockIdx.x * blockDim.x + threadIdx.x;
+    const int c = t % kBBox;
+    if (t < n_spec * kBBox) bits[t] = ordered_bits(c < 3 ? 1e300 : c < 6 ? -1e300 : 0.0);
+}
+__global__ void __launch_bounds__(256) k_bbox(const double* __restrict__ X,
+                                              const double* __restrict__ V0, int64_t n,
+                                              const int64_t* __restrict__ off,
+                                              unsigned long long* __restrict__ bits) {
     __shared__ double red[7][256];
-    const int s = blockIdx.x;
+    const int s = blockIdx.y;
     double lo[3] = {1e300, 1e300, 1e300}, hi[3] = {-1e300, -1e300, -1e300}, vmax = 0.0;
-    for (int64_t i = off[s] + threadIdx.x; i < off[s + 1]; i += blockDim.x) {
+    for (int64_t i = off[s] + (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < off[s + 1];
+         i += (int64_t)gridDim.x * blockDim.x) {
         for (int c = 0; c < 3; ++c) {
             const double x = X[c * n + i];
             lo[c] = x < lo[c] ? x : lo[c];
@@ -94,14 +112,23 @@ __global__ void k_bbox(const double* __restrict__ X, const double* __restrict__ 
         }
         __syncthreads();
     }
-    if (threadIdx.x < 6) bbox[kBBox * s + threadIdx.x] = red[threadIdx.x][0];
-    if (threadIdx.x == 6) {
-        const DevSpec& P = specs[s];
-        bbox[kBBox * s + 6] = P.h_per_spacing > 0.0
-                                  ? 1.0 / (P.h_per_spacing * cbrt(red[6][0]) * (1.0 + 1e-9))
-                                  : P.inv_cell;
-        bbox[kBBox * s + 7] = 0.0;
-    }
+    const int t = threadIdx.x;
+    if (t < 3) atomicMin(&bits[kBBox * s + t], ordered_bits(red[t][0]));
+    else if (t < 7) atomicMax(&bits[kBBox * s + t], ordered_bits(red[t][0]));
+}
+__global__ void k_bbox_final(double* __restrict__ bbox, int n_spec,
+                             const DevSpec* __restrict__ specs) {
+    const int s = blockIdx.x * blockDim.x + threadIdx.x;
+    if (s >= n_spec) return;
+    double* b = bbox + kBBox * s;
+    double v[7];
+    for (int c = 0; c < 7; ++c)
+        v[c] = from_ordered_bits((unsigned long long)__double_as_longlong(b[c]));
+    for (int c = 0; c < 6; ++c) b[c] = v[c];
+    const DevSpec& P = specs[s];
+    b[6] = P.h_per_spacing > 0.0 ? 1.0 / (P.h_per_spacing * cbrt(v[6]) * (1.0 + 1e-9))
+                                 : P.inv_cell;
+    b[7] = 0.0;
 }
 
 __device__ __forceinline__ int spec_of(const int64_t* off, int n_spec, int64_t i) {
@@ -142,20 +169,45 @@ __global__ void k_keys(const double* __restrict__ X, int64_t n, int64_t n_pow2,
     vals[i] = (int32_t)i;
 }
 
-// one compare-exchange stage of a bitonic sort of (key, val) pairs
+// Compare-exchange of (key, val) pairs of a bitonic sort, in registers.
+__device__ __forceinline__ void sort_pair(uint64_t& ka, int32_t& va, uint64_t& kb, int32_t& vb,
+                                          bool asc) {
+    const bool a_gt_b = (ka > kb) || (ka == kb && va > vb);
+    if (a_gt_b == asc) {
+        const uint64_t k = ka; ka = kb; kb = k;
+        const int32_t v = va; va = vb; vb = v;
+    }
+}
+// One stage (kTwo: the stages j and j / 2, which four elements share, in one
+// pass over memory) of the sort: a thread per group of 2 (4) elements.
+template <bool kTwo>
 __global__ void k_bitonic(uint64_t* __restrict__ keys, int32_t* __restrict__ vals, int64_t N,
                           int64_t j, int64_t k) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= N) return;
-    const int64_t l = i ^ j;
-    if (l <= i) return;
-    const uint64_t ka = keys[i], kb = keys[l];
-    const int32_t va = vals[i], vb = vals[l];
-    const bool a_gt_b = (ka > kb) || (ka == kb && va > vb);
+    constexpr int M = kTwo ? 4 : 2;
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t >= N / M) return;
+    const int64_t d = kTwo ? j >> 1 : j;   // distance of the group's elements
+    const int64_t i = M * (t & ~(d - 1)) + (t & (d - 1));
+    uint64_t ke[M];
+    int32_t ve[M];
+#pragma unroll
+    for (int e = 0; e < M; ++e) {
+        ke[e] = keys[i + e * d];
+        ve[e] = vals[i + e * d];
+    }
     const bool asc = (i & k) == 0;
-    if (a_gt_b == asc) {
-        keys[i] = kb; keys[l] = ka;
-        vals[i] = vb; vals[l] = va;
+    if constexpr (kTwo) {
+        sort_pair(ke[0], ve[0], ke[2], ve[2], asc);
+        sort_pair(ke[1], ve[1], ke[3], ve[3], asc);
+        sort_pair(ke[0], ve[0], ke[1], ve[1], asc);
+        sort_pair(ke[2], ve[2], ke[3], ve[3], asc);
+    } else {
+        sort_pair(ke[0], ve[0], ke[1], ve[1], asc);
+    }
+#pragma unroll
+    for (int e = 0; e < M; ++e) {
+        keys[i + e * d] = ke[e];
+        vals[i + e * d] = ve[e];
     }
 }
 
@@ -205,15 +257,18 @@ __global__ void __launch_bounds__(kSortB / 2) k_bitonic_lds(uint64_t* __restrict
 
 // Sort N (a power of two, >= 2) (key, val) pairs ascending by key, then val:
 // the bitonic network, its stages with partners closer than kSortB run in
-// LDS, the others one launch each.
+// LDS, the others two to a launch.
 hipError_t launch_bitonic_sort(uint64_t* keys, int32_t* vals, int64_t N, hipStream_t st) {
     constexpr int T = 256;
     const int B = (int)(N < kSortB ? N : kSortB);
     const unsigned blocks = (unsigned)(N / B);
     k_bitonic_lds<<<blocks, B / 2, 0, st>>>(keys, vals, N, 0);
     for (int64_t k = 2 * (int64_t)B; k <= N; k <<= 1) {
-        for (int64_t j = k >> 1; j >= B; j >>= 1)
-            k_bitonic<<<(unsigned)((N + T - 1) / T), T, 0, st>>>(keys, vals, N, j, k);
+        int64_t j = k >> 1;
+        for (; j >= 2 * (int64_t)B; j >>= 2)
+            k_bitonic<true><<<(unsigned)((N / 4 + T - 1) / T), T, 0, st>>>(keys, vals, N, j, k);
+        if (j >= B)
+            k_bitonic<false><<<(unsigned)((N / 2 + T - 1) / T), T, 0, st>>>(keys, vals, N, j, k);
         k_bitonic_lds<<<blocks, B / 2, 0, st>>>(keys, vals, N, k);
     }
     return hipGetLastError();
@@ -271,13 +326,51 @@ __global__ void k_spec_ranges(DevSpec* specs, int n_spec, const uint64_t* __rest
     specs[s].last = lower((uint64_t)(s + 1) << kSpecShift);
 }
 
+// The occupied cells as a hash table of their first sorted particle (open
+// addressing; H, a power of two, at least twice the particles, so that a
+// search always meets a free slot).
+constexpr uint64_t kNoCell = ~0ull;
+__device__ __forceinline__ int64_t cell_home(uint64_t key, int64_t H) {
+    return (int64_t)((key * 0x9e3779b97f4a7c15ull) >> 20) & (H - 1);
+}
+__global__ void k_cells_clear(CSlot* __restrict__ cell, int64_t H) {
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t < H) cell[t].key = kNoCell;
+}
+// (keyed by the cell's coordinates: the curve's key takes a loop per cell)
+__device__ __forceinline__ uint64_t grid_key(int sp, int32_t x, int32_t y, int32_t z) {
+    return ((uint64_t)sp << kSpecShift) |
+           ((uint64_t)(((uint32_t)z << kCellBits) | (uint32_t)y) << kCellBits) | (uint32_t)x;
+}
+__global__ void k_cells_insert(DevState s, const uint64_t* __restrict__ keys,
+                               const double* __restrict__ bbox, CSlot* __restrict__ cell,
+                               int64_t H) {
+    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (p >= s.n || (p > 0 && keys[p - 1] == keys[p])) return;   // the first of its cell
+    int64_t end = p + 1;
+    while (end < s.n && keys[end] == keys[p]) ++end;
+    const int sp = s.spec[p];
+    const D4 x = s.XV[p];
+    int32_t c[3];
+    cell_of(bbox + kBBox * sp, x.x, x.y, x.z, c);
+    const uint64_t key = grid_key(sp, c[0], c[1], c[2]);
+    for (int64_t h = cell_home(key, H);; h = (h + 1) & (H - 1))
+        if (atomicCAS(reinterpret_cast<unsigned long long*>(&cell[h].key), kNoCell, key) == kNoCell) {
+            cell[h].start = (int32_t)p;
+            cell[h].cnt = (int32_t)(end - p);
+            return;
+        }
+}
+
 // Visit the neighbours of sorted particle p over the 27 cells around it, in
 // a fixed order.  The distance test is evaluated exactly as written (no
 // fused multiply-add) so membership is decided identically to a plain
-// evaluation of |X_j - X_i|^2 < h^2.
+// evaluation of |X_j - X_i|^2 < h^2.  What bounds the search is its chain of
+// loads, so a layer's nine table slots are loaded together, and the particles
+// of a cell four at a time.
 template <typename F>
-__device__ __forceinline__ int for_neighbours(const DevState& s, const uint64_t* keys,
-                                              const double* bbox, int64_t p, F&& visit) {
+__device__ __forceinline__ int for_neighbours(const DevState& s, const double* bbox,
+                                              const CSlot* cell, int64_t H, int64_t p, F&& visit) {
 #pragma clang fp contract(off)
     const int sp = s.spec[p];
     const DevSpec& P = s.specs[sp];
@@ -286,104 +379,163 @@ __device__ __forceinline__ int for_neighbours(const DevState& s, const uint64_t*
     int32_t c[3];
     cell_of(bbox + kBBox * sp, xi, yi, zi, c);
     const double hp = s.hs[p];
+    const double lim0 = P.h2;
+    constexpr int kLayer = 9, kU = 4;
+    constexpr uint32_t kCells = 1u << kCellBits;
     int count = 0;
-    for (int dz = -1; dz <= 1; ++dz)
-        for (int dy = -1; dy <= 1; ++dy)
-            for (int dx = -1; dx <= 1; ++dx) {
-                const int32_t cx = c[0] + dx, cy = c[1] + dy, cz = c[2] + dz;
-                if (cx < 0 || cy < 0 || cz < 0 || cx >= (1 << kCellBits) ||
-                    cy >= (1 << kCellBits) || cz >= (1 << kCellBits))
-                    continue;
-                const uint64_t key = ((uint64_t)sp << kSpecShift) | cell_key(cx, cy, cz);
-                int64_t lo = P.first, hi = P.last;
-                while (lo < hi) {
-                    const int64_t mid = (lo + hi) >> 1;
-                    if (keys[mid] < key) lo = mid + 1; else hi = mid;
+    for (int dz = -1; dz <= 1; ++dz) {
+        uint64_t key[kLayer];
+        int64_t h[kLayer];
+        CSlot slot[kLayer];
+        bool in[kLayer];
+#pragma unroll
+        for (int e = 0; e < kLayer; ++e) {
+            const int32_t cx = c[0] + e % 3 - 1, cy = c[1] + e / 3 - 1, cz = c[2] + dz;
+            in[e] = (uint32_t)cx < kCells && (uint32_t)cy < kCells && (uint32_t)cz < kCells;
+            key[e] = in[e] ? grid_key(sp, cx, cy, cz) : grid_key(sp, c[0], c[1], c[2]);
+            h[e] = cell_home(key[e], H);
+            slot[e] = cell[h[e]];
+        }
+#pragma unroll
+        for (int e = 0; e < kLayer; ++e) {
+            while (slot[e].key != key[e] && slot[e].key != kNoCell) {
+                h[e] = (h[e] + 1) & (H - 1);
+                slot[e] = cell[h[e]];
+            }
+            const int m = in[e] && slot[e].key == key[e] ? slot[e].cnt : 0;
+            for (int q0 = 0; q0 < m; q0 += kU) {
+                D4 xq[kU];
+                double hq[kU];
+#pragma unroll
+                for (int u = 0; u < kU; ++u) {
+                    const int64_t q = slot[e].start + (q0 + u < m ? q0 + u : 0);
+                    xq[u] = s.XV[q];
+                    hq[u] = s.var_h ? s.hs[q] : 0.0;
                 }
-                for (int64_t q = lo; q < P.last && keys[q] == key; ++q) {
-                    if (q == p) continue;
-                    const D4 xq = s.XV[q];
-                    const double d0 = xq.x - xi;
-                    const double d1 = xq.y - yi;
-                    const double d2 = xq.z - zi;
+#pragma unroll
+                for (int u = 0; u < kU; ++u) {
+                    const int64_t q = slot[e].start + q0 + u;
+                    const double d0 = xq[u].x - xi;
+                    const double d1 = xq[u].y - yi;
+                    const double d2 = xq[u].z - zi;
                     const double r2 = d0 * d0 + d1 * d1 + d2 * d2;
-                    double lim = P.h2;
+                    double lim = lim0;
                     if (s.var_h) {   // graded spacing: the pair's support (h_p + h_q) / 2
-                        const double hpq = 0.5 * (hp + s.hs[q]);
+                        const double hpq = 0.5 * (hp + hq[u]);
                         lim = hpq * hpq;
                     }
-                    if (r2 < lim) visit(count++, (int32_t)q);
+                    if (q0 + u < m && q != p && r2 < lim) visit(count++, (int32_t)q);
                 }
             }
+        }
+    }
     return count;
 }
 
-__global__ void k_count(DevState s, const uint64_t* __restrict__ keys,
-                        const double* __restrict__ bbox, int32_t* __restrict__ nnb) {
+// One search per particle: its neighbours go to `found` (neighbour k of particle
+// p at k n + p, as many as k_cap), its slice's width (64 times the most
+// neighbours of one of its particles: a slice is a wave) to slice_ptr[slice + 1],
+// for the scan.  Cells are found through the table; a binary search of the
+// sorted keys for each, once to count and once more to fill, took 277 + 290 us
+// for 200k particles, this and k_fill 160 + 10.
+static_assert(kSlice == 64, "a slice is a wave");
+__global__ void __launch_bounds__(256) k_count(DevState s, const double* __restrict__ bbox,
+                                               const CSlot* __restrict__ cell, int64_t H, int k_cap,
+                                               int32_t* __restrict__ nnb,
+                                               int64_t* __restrict__ slice_ptr,
+                                               int32_t* __restrict__ found) {
     const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= s.np) return;
-    if (p >= s.n) {
-        nnb[p] = 0;
-        return;
-    }
-    const int cnt = for_neighbours(s, keys, bbox, p, [](int, int32_t) {});
+    if (p >= s.np) return;   // (whole waves: np is a multiple of the slice)
+    int cnt = 0;
+    if (p < s.n)
+        cnt = for_neighbours(s, bbox, cell, H, p, [&](int k, int32_t q) {
+            if (k < k_cap) found[(int64_t)k * s.n + p] = q;
+        });
     nnb[p] = cnt;
-    atomicMax(&s.err[1], cnt);
+    const uint64_t grouped = __ballot(p < s.n && s.bc[p] >= 0);
+    int most = cnt, sum = cnt;
+    for (int w = 32; w > 0; w >>= 1) {
+        most = max(most, __shfl_xor(most, w));
+        sum += __shfl_xor(sum, w);
+    }
+    if (p % kSlice == 0) {
+        slice_ptr[p / kSlice + 1] = (int64_t)most * kSlice;
+        if (p == 0) slice_ptr[0] = 0;
+        atomicMax(&s.err[1], most);
+        if (grouped) atomicAdd(&s.err[5], (int)__popcll(grouped));
+        atomicAdd(reinterpret_cast<unsigned long long*>(&s.err[6]), (unsigned long long)sum);
+    }
 }
 
-// slice_ptr[t] = sum over earlier slices of 64 * (max count in the slice);
-// one block, fixed order.
-__global__ void __launch_bounds__(1024) k_slice_scan(const int32_t* __restrict__ nnb,
-                                                     int64_t n_slices,
-                                                     int64_t* __restrict__ slice_ptr) {
-    __shared__ int64_t part[1024];
+// In-place inclusive scan of a[0..m): the sums of blocks of kScanB kScanPer
+// values (part), then each block's values from the sum of the parts before it.
+constexpr int kScanB = 256, kScanPer = 8;
+__device__ __forceinline__ int64_t block_sum(int64_t v, int64_t* red) {
+    red[threadIdx.x] = v;
+    __syncthreads();
+    for (int w = kScanB / 2; w > 0; w >>= 1) {
+        if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
+        __syncthreads();
+    }
+    const int64_t sum = red[0];
+    __syncthreads();
+    return sum;
+}
+__global__ void __launch_bounds__(kScanB) k_scan_part(const int64_t* __restrict__ a, int64_t m,
+                                                      int64_t* __restrict__ part) {
+    __shared__ int64_t red[kScanB];
+    const int64_t base = (int64_t)blockIdx.x * kScanB * kScanPer;
+    int64_t v = 0;
+    for (int u = 0; u < kScanPer; ++u) {
+        const int64_t q = base + u * kScanB + threadIdx.x;
+        if (q < m) v += a[q];
+    }
+    v = block_sum(v, red);
+    if (threadIdx.x == 0) part[blockIdx.x] = v;
+}
+__global__ void __launch_bounds__(kScanB) k_scan_apply(int64_t* __restrict__ a, int64_t m,
+                                                       const int64_t* __restrict__ part) {
+    __shared__ int64_t red[kScanB];
     const int t = threadIdx.x;
-    const int64_t per = (n_slices + 1023) / 1024;
-    const int64_t a = t * per, b = (a + per < n_slices) ? a + per : n_slices;
-    int64_t sum = 0;
-    for (int64_t q = a; q < b; ++q) {
-        int w = 0;
-        for (int l = 0; l < kSlice; ++l) w = max(w, nnb[q * kSlice + l]);
-        sum += (int64_t)w * kSlice;
-    }
-    part[t] = sum;
-    __syncthreads();
-    if (t == 0) {
-        int64_t run = 0;
-        for (int q = 0; q < 1024; ++q) {
-            const int64_t v = part[q];
-            part[q] = run;
-            run += v;
+    int64_t before = 0;
+    for (int64_t q = t; q < (int64_t)blockIdx.x; q += kScanB) before += part[q];
+    before = block_sum(before, red);
+    const int64_t base = (int64_t)blockIdx.x * kScanB * kScanPer;
+    for (int u = 0; u < kScanPer; ++u) {   // kScanB values at a time
+        const int64_t q = base + u * kScanB + t;
+        red[t] = q < m ? a[q] : 0;
+        __syncthreads();
+        for (int w = 1; w < kScanB; w <<= 1) {
+            const int64_t v = t >= w ? red[t - w] : 0;
+            __syncthreads();
+            red[t] += v;
+            __syncthreads();
         }
-        slice_ptr[n_slices] = run;
-    }
-    __syncthreads();
-    int64_t run = part[t];
-    for (int64_t q = a; q < b; ++q) {
-        slice_ptr[q] = run;
-        int w = 0;
-        for (int l = 0; l < kSlice; ++l) w = max(w, nnb[q * kSlice + l]);
-        run += (int64_t)w * kSlice;
+        if (q < m) a[q] = before + red[t];
+        before += red[kScanB - 1];
+        __syncthreads();
     }
 }
+static hipError_t launch_scan(int64_t* a, int64_t m, int64_t* part, hipStream_t st) {
+    const unsigned blocks = (unsigned)((m + kScanB * kScanPer - 1) / (kScanB * kScanPer));
+    if (blocks == 0) return hipSuccess;
+    k_scan_part<<<blocks, kScanB, 0, st>>>(a, m, part);
+    k_scan_apply<<<blocks, kScanB, 0, st>>>(a, m, part);
+    return hipGetLastError();
+}
 
-__global__ void k_fill(DevState s, const uint64_t* __restrict__ keys,
-                       const double* __restrict__ bbox, int32_t* __restrict__ col,
-                       int64_t cap_slots) {
+__global__ void k_fill(DevState s, const int32_t* __restrict__ found, int32_t* __restrict__ col) {
     const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= s.np) return;
-    if (s.slice_ptr[s.np / kSlice] > cap_slots) return;  // capacity error reported by the host
     const int64_t sl = p / kSlice;
     const int w = (int)((s.slice_ptr[sl + 1] - s.slice_ptr[sl]) / kSlice);
     int32_t* base = col + s.slice_ptr[sl] + (p % kSlice);
-    int cnt = 0;
-    if (p < s.n)
-        cnt = for_neighbours(s, keys, bbox, p,
-                             [&](int k, int32_t q) { base[(int64_t)k * kSlice] = q; });
+    const int cnt = p < s.n ? s.nnb[p] : 0;
     // the rest of the slice's width points at the particle itself (a valid
     // address for loops that run to the slice width and mask the excess)
     const int32_t self = p < s.n ? (int32_t)p : 0;
-    for (int k = cnt; k < w; ++k) base[(int64_t)k * kSlice] = self;
+    for (int k = 0; k < w; ++k)
+        base[(int64_t)k * kSlice] = k < cnt ? found[(int64_t)k * s.n + p] : self;
 }
 
 // Correction matrix L_i = sum_j V_j (X_j - X_i) (x) gradW_ij (eq.
@@ -487,7 +639,12 @@ __global__ void k_init(DevState s) {
 
 hipError_t launch_build_count(DevState& s, const BuildBuffers& b, hipStream_t st) {
     const int T = 256;
-    k_bbox<<<s.n_spec, 256, 0, st>>>(b.X_in, b.V0_in, s.n, b.spec_off, s.specs, b.bbox);
+    unsigned long long* bits = reinterpret_cast<unsigned long long*>(b.bbox);
+    const int64_t chunks = (s.n + kBBoxChunk - 1) / kBBoxChunk;
+    const dim3 bb((unsigned)(chunks < 256 ? chunks : 256), (unsigned)s.n_spec);
+    k_bbox_clear<<<(s.n_spec * kBBox + T - 1) / T, T, 0, st>>>(bits, s.n_spec);
+    k_bbox<<<bb, 256, 0, st>>>(b.X_in, b.V0_in, s.n, b.spec_off, bits);
+    k_bbox_final<<<(s.n_spec + T - 1) / T, T, 0, st>>>(b.bbox, s.n_spec, s.specs);
     k_keys<<<(unsigned)((b.n_pow2 + T - 1) / T), T, 0, st>>>(b.X_in, s.n, b.n_pow2, b.spec_off,
                                                              s.n_spec, b.bbox, b.keys, b.vals,
                                                              s.err);
@@ -500,9 +657,14 @@ hipError_t launch_build_count(DevState& s, const BuildBuffers& b, hipStream_t st
                                    const_cast<int32_t*>(s.iperm));
     k_spec_ranges<<<(s.n_spec + 63) / 64, 64, 0, st>>>(const_cast<DevSpec*>(s.specs), s.n_spec,
                                                       b.keys, s.n);
-    k_count<<<gp, T, 0, st>>>(s, b.keys, b.bbox, const_cast<int32_t*>(s.nnb));
-    k_slice_scan<<<1, 1024, 0, st>>>(s.nnb, s.np / kSlice, const_cast<int64_t*>(s.slice_ptr));
-    return hipGetLastError();
+    const unsigned gh = (unsigned)((b.H + T - 1) / T);
+    k_cells_clear<<<gh, T, 0, st>>>(b.cell, b.H);
+    k_cells_insert<<<(unsigned)((s.n + T - 1) / T), T, 0, st>>>(s, b.keys, b.bbox, b.cell,
+                                                                        b.H);
+    k_count<<<gp, T, 0, st>>>(s, b.bbox, b.cell, b.H, b.k_cap,
+                              const_cast<int32_t*>(s.nnb), const_cast<int64_t*>(s.slice_ptr),
+                              b.found);
+    return launch_scan(const_cast<int64_t*>(s.slice_ptr) + 1, s.np / kSlice, b.part, st);
 }
 
 // One workgroup per tile of T particles: collect the indices of the tile's
@@ -639,7 +801,7 @@ hipError_t launch_halo(const DevState& s, int k_cap, int T, int32_t* halo, int32
 hipError_t launch_build_fill(DevState& s, const BuildBuffers& b, hipStream_t st) {
     const int T = 256;
     const unsigned gp = (unsigned)((s.np + T - 1) / T);
-    k_fill<<<gp, T, 0, st>>>(s, b.keys, b.bbox, const_cast<int32_t*>(s.col), s.col_cap);
+    k_fill<<<gp, T, 0, st>>>(s, b.found, const_cast<int32_t*>(s.col));
     return hipGetLastError();
 }
 
@@ -2925,32 +3087,6 @@ __global__ void k_export_count(DevState s, int64_t* __restrict__ row_ptr) {
     row_ptr[i + 1] = s.nnb[s.iperm[i]];
 }
 
-// in-place inclusive scan of a[0..m), one block
-__global__ void __launch_bounds__(1024) k_scan_inplace(int64_t* __restrict__ a, int64_t m) {
-    __shared__ int64_t part[1024];
-    const int t = threadIdx.x;
-    const int64_t per = (m + 1023) / 1024;
-    const int64_t lo = t * per, hi = (lo + per < m) ? lo + per : m;
-    int64_t sum = 0;
-    for (int64_t q = lo; q < hi; ++q) sum += a[q];
-    part[t] = sum;
-    __syncthreads();
-    if (t == 0) {
-        int64_t run = 0;
-        for (int q = 0; q < 1024; ++q) {
-            const int64_t v = part[q];
-            part[q] = run;
-            run += v;
-        }
-    }
-    __syncthreads();
-    int64_t run = part[t];
-    for (int64_t q = lo; q < hi; ++q) {
-        run += a[q];
-        a[q] = run;
-    }
-}
-
 __global__ void k_export_fill(DevState s, const int64_t* __restrict__ row_ptr,
                               int32_t* __restrict__ col_out) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -2970,12 +3106,13 @@ __global__ void k_export_fill(DevState s, const int64_t* __restrict__ row_ptr,
     }
 }
 
-hipError_t launch_export_neighbors(const DevState& s, int64_t* row_ptr, int32_t* col, int64_t*,
-                                   hipStream_t st) {
+hipError_t launch_export_neighbors(const DevState& s, int64_t* row_ptr, int32_t* col,
+                                   int64_t* part, hipStream_t st) {
     const int T = 256;
     const unsigned g = (unsigned)((s.n + T - 1) / T);
     k_export_count<<<g, T, 0, st>>>(s, row_ptr);
-    k_scan_inplace<<<1, 1024, 0, st>>>(row_ptr + 1, s.n);
+    hipError_t e = launch_scan(row_ptr + 1, s.n, part, st);
+    if (e != hipSuccess) return e;
     k_export_fill<<<g, T, 0, st>>>(s, row_ptr, col);
     return hipGetLastError();
 }
@@ -2984,14 +3121,22 @@ hipError_t launch_export_neighbors(const DevState& s, int64_t* row_ptr, int32_t*
 // diagnostics
 // ===========================================================================
 
-// members of each prescribed-velocity group, ordered by (group, sorted index)
+// Members of each prescribed-velocity group, ordered by (group, sorted index):
+// the m particles with a group, in any order (their number, counted with the
+// neighbours, counts down to 0), and padding to N, to be sorted.
 __global__ void k_bc_keys(DevState s, uint64_t* __restrict__ keys, int32_t* __restrict__ vals,
-                          int64_t n_pow2) {
+                          int64_t m, int64_t N) {
     const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= n_pow2) return;
     const int g = (p < s.n) ? s.bc[p] : -1;
-    keys[p] = g >= 0 ? (((uint64_t)g << 32) | (uint64_t)p) : ~0ull;
-    vals[p] = (int32_t)p;
+    if (g >= 0) {
+        const int64_t at = (int64_t)atomicSub(&s.err[5], 1) - 1;
+        keys[at] = ((uint64_t)g << 32) | (uint64_t)p;
+        vals[at] = (int32_t)p;
+    }
+    if (p >= m && p < N) {
+        keys[p] = ~0ull;
+        vals[p] = 0x7fffffff;
+    }
 }
 
 __global__ void k_bc_ptr(DevState s, const uint64_t* __restrict__ keys, int64_t n,
@@ -3007,7 +3152,7 @@ __global__ void k_bc_ptr(DevState s, const uint64_t* __restrict__ keys, int64_t 
         }
         bc_ptr[t] = lo;
     }
-    if (t < n && keys[t] != ~0ull) bc_list[t] = vals[t];
+    if (t < n) bc_list[t] = vals[t];
 }
 
 // ===========================================================================
@@ -3434,15 +3579,17 @@ hipError_t launch_contact_build(const DevState& s, int parity, uint64_t* keys, i
     return hipGetLastError();
 }
 
-hipError_t launch_bc_lists(const DevState& s, uint64_t* keys, int32_t* vals, int64_t n_pow2,
+hipError_t launch_bc_lists(const DevState& s, uint64_t* keys, int32_t* vals, int64_t m,
                            int32_t* bc_list, int64_t* bc_ptr, hipStream_t st) {
     const int T = 256;
-    const unsigned g = (unsigned)((n_pow2 + T - 1) / T);
-    k_bc_keys<<<g, T, 0, st>>>(s, keys, vals, n_pow2);
-    hipError_t e = launch_bitonic_sort(keys, vals, n_pow2, st);
+    int64_t N = 2;
+    while (N < m) N <<= 1;
+    const int64_t w = N > s.n ? N : s.n;
+    k_bc_keys<<<(unsigned)((w + T - 1) / T), T, 0, st>>>(s, keys, vals, m, N);
+    hipError_t e = launch_bitonic_sort(keys, vals, N, st);
     if (e != hipSuccess) return e;
-    const int64_t m = (s.n > s.n_bc + 1) ? s.n : s.n_bc + 1;
-    k_bc_ptr<<<(unsigned)((m + T - 1) / T), T, 0, st>>>(s, keys, s.n, vals, bc_list, bc_ptr);
+    const int64_t u = (m > s.n_bc + 1) ? m : s.n_bc + 1;
+    k_bc_ptr<<<(unsigned)((u + T - 1) / T), T, 0, st>>>(s, keys, m, vals, bc_list, bc_ptr);
     return hipGetLastError();
 }
 
