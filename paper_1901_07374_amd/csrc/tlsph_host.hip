@@ -838,6 +838,11 @@ tlsph_status tlsph_build_neighbors(tlsph_ctx* c, const double* X, const double* 
             c->st.staged = 1;
             c->block_b = c->st.tile * c->sub_b;
         }
+        // The deformation pass until it is tuned or set: workgroups of 64 while
+        // larger ones leave CUs idle (25k particles FP64: 12.6 us, in blocks of
+        // 256 15.0, staged 13.4), else staged over the force pass's tiles (61k:
+        // 16.2 us, unstaged 17.4; 391k: 50.6 and 71.3).
+        c->block_a = L.n <= 128 * (int64_t)n_cu ? 64 : c->st.staged_lds_a ? 0 : 256;
     }
     // group sizes to the host
     std::vector<int64_t> bptr((size_t)L.n_bc + 1, 0);
