@@ -454,18 +454,19 @@ tlsph_status build_tile_lists(tlsph_ctx* c, int T, size_t halo, size_t halo_cnt,
 
 // The form of the staged force pass at the current tiles with `sub` lanes per
 // particle; every form gives the same bits.  Measured on whole passes:
-// - pipelined over as many workgroups as fit (two lanes, one support for all,
-//   every particle's pairs within its registers, the image in LDS) where a CU
-//   then works on at least 160 particles at a time (FP64, 4.1M particles:
-//   tiles of 256 631 us, of 128, one to a CU, 851 against 757 in two sweeps) and
-//   the walk is long enough for its uneven end: four tiles a workgroup (200k
-//   FP64, tiles of 196: 39.8 us, 48.4 in two sweeps), eight in the mixed form
-//   (4.1M: 511 us, 607 in one sweep; 200k, three or four tiles: 30.9, 29.0).
 // - FP64, two sweeps where their smaller image lets more workgroups share a CU
 //   and the tiles need the room (395k particles, tiles of 97, three instead of
-//   two: 99.8 us, 118 in one sweep).
-// - else one sweep: one barrier instead of three (25k particles FP64, every
-//   tile resident at once: 12.6 us, 13.3 in two sweeps).
+//   two: 99.8 us, 118 in one sweep); else one sweep: one barrier instead of
+//   three (25k particles FP64, every tile resident at once: 12.6 us, 13.3 in two
+//   sweeps).
+// - In their place, pipelined over as many workgroups as fit (two lanes, one
+//   support for all, every particle's pairs within its registers, the image in
+//   LDS) where that is as many to a CU as the other form has (FP64: or 160
+//   particles to a CU), and each takes three tiles or more.  FP64, 4.1M particles: tiles of 256, one to a CU either
+//   way, 631 us; tiles of 128, one against two, 851 and 757; 200k, tiles of 160,
+//   one against two, 45.5 and 53.7.  Mixed: plate 2M,
+//   tiles of 128, two and two, 255 and 309; tiles of 192, one and two, 308 and
+//   295; plate 0.5M, tiles of 128, two and three, 63.4 and 61.5.
 tlsph_status set_form_b(tlsph_ctx* c, int sub) {
     const Layout& L = c->L;
     const bool var_h = c->st.var_h != 0;
@@ -486,7 +487,9 @@ tlsph_status set_form_b(tlsph_ctx* c, int sub) {
         HIPCHK(c, prepare_staged(pipe));
         HIPCHK(c, staged_blocks_per_cu(L.mixed, c->st.tile * sub, pipe, &per_cu));
         const int64_t room = (int64_t)c->n_cu * per_cu;
-        if (per_cu * c->st.tile >= 160 && 2 * tiles > (L.mixed ? 15 : 7) * room) {
+        const bool many = per_cu >= (int)(lds / c->lds_b) ||
+                          (!L.mixed && per_cu * c->st.tile >= 160);
+        if (many && 2 * tiles > 5 * room) {
             c->st.form_b = kFormPipe;
             c->lds_b = pipe;
             c->st.grid_b = (int32_t)room;

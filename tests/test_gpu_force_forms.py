@@ -40,14 +40,15 @@ PROBLEMS = {
 }
 # problem, precision, lanes, tile, the form it takes
 CASES = [
-    ("bar", "fp64", 2, 160, "pipe"), ("bar", "fp64", 2, 163, "pipe"),
+    ("bar", "fp64", 2, 163, "pipe"), ("bar", "fp64", 2, 192, "pipe"), ("bar", "fp64", 2, 195, "pipe"),
     ("bar", "fp64", 2, 66, "two"), ("bar", "fp64", 4, 65, "two"), ("bar", "fp64", 1, 66, "two"),
     ("bar", "fp64", 2, 96, "one"), ("bar", "fp64", 1, 100, "one"),
-    ("bar_large", "mixed", 2, 96, "pipe"), ("bar_large", "mixed", 2, 195, "pipe"),
-    ("bar", "mixed", 2, 128, "one"), ("bar", "mixed", 4, 100, "one"),
+    ("bar_large", "mixed", 2, 128, "pipe"), ("bar_large", "mixed", 2, 227, "pipe"),
+    ("bar_large", "mixed", 2, 195, "one"),
+    ("bar", "mixed", 2, 100, "one"), ("bar", "mixed", 4, 100, "one"),
     ("wide", "fp64", 2, 66, "one"), ("wide", "mixed", 2, 66, "one"),
     ("wide_large", "fp64", 2, 67, "two"), ("wide_large", "fp64", 4, 64, "two"),
-    ("contact_av", "fp64", 2, 192, "pipe"), ("stopped", "fp64", 2, 161, "pipe"),
+    ("contact_av", "fp64", 2, 192, "pipe"), ("stopped", "fp64", 2, 193, "pipe"),
 ]
 
 
