@@ -267,19 +267,28 @@ __host__ __device__ __forceinline__ void hardening_and_slope(const DevSpec& P, d
 // unique; Newton steps are kept inside the shrinking bracket (bisection when
 // a step leaves it), at most P.newton_impl (100 by default) iterations.  They
 // start at the increment of the last step's rate, d_last, where it lies in the
-// bracket: plastic flow changes little in a step, while from d_max, far above
-// the root at high rates, Newton leaves the bracket and bisects first (200k
-// particles with Voce hardening, tiles of 64: the deformation pass 65.4 us,
-// about 12 iterations; so 58.5).  The iteration ends on a Newton step below
-// 1e-8 of d (Newton converges quadratically here, g being smooth with |g''| d
-// of the order of |g'|, so the next correction would be below about 1e-16 d),
-// on any step below 1e-14 of d or of seq / k3 (the increment that would unload
-// the trial stress, which sets the rounding of g: a tiny d cannot be resolved
-// to 1e-14 of itself), or on a bracket that narrow.
+// bracket (plastic flow changes little in a step), unless the caller has set a
+// lower cap: its iterations count from d_max, where a jump of the rate cannot
+// cost one more.  The iteration ends on a Newton step below 1e-8 of d (Newton
+// converges quadratically here, g being smooth with |g''| d of the order of
+// |g'|, so the next correction would be below about 1e-16 d) or below 1e-14 of
+// seq / k3 (the increment that would unload the trial stress, which sets the
+// rounding of g: a tiny d cannot be resolved to 1e-14 of itself).  That test
+// comes before the bracket's: the iterate has just become one of its ends, so a
+// converged step, of zero or of an ulp past that end, would count as leaving it
+// and send the root back into bisection (over rates of 1 to 3e5 /s the error
+// from any start was 7e-16 to 2e-15 of seq / k3 rms, and 46 % of the starts
+// within 1e-7 of the root took over three iterations; so 4e-17 to 6e-17, at most
+// three; 200k particles with Voce hardening, the deformation pass: 70.9 us from
+// d_max, 62.1 from d_last, so 52.3).  A bisection ends where it cannot resolve d
+// either.
+constexpr int kNewtonImpl = 100;   // the default cap
 __host__ __device__ inline double implicit_increment(const DevSpec& P, double k3, double omD,
                                                      double seq, double eps, double d_max,
                                                      double d_last, int32_t& flags) {
-    double lo = 0.0, hi = d_max, d = d_last > 0.0 && d_last < d_max ? d_last : d_max;
+    double lo = 0.0, hi = d_max, d = d_max;
+    if (P.newton_impl >= kNewtonImpl && d_last > 0.0 && d_last < d_max) d = d_last;
+    const double tiny = 1e-14 * seq / k3;
     for (int it = 0; it < P.newton_impl; ++it) {
         const double rs = d * P.inv_dt * P.inv_eps_dot0;
         const bool fast = rs > 1.0 && P.C != 0.0;
@@ -291,13 +300,11 @@ __host__ __device__ inline double implicit_increment(const DevSpec& P, double k3
         const double drf = fast ? P.C * rcp_nr(d) : 0.0;
         const double dg = -k3 - omD * (hp * rf + h * drf);
         double nd = d - g * rcp_nr(dg);
-        const bool newton = nd > lo && nd < hi;
-        if (!newton) nd = 0.5 * (lo + hi);
+        if (fabs(nd - d) <= 1e-8 * d || fabs(nd - d) <= tiny) return nd < lo ? lo : nd > hi ? hi : nd;
+        if (!(nd > lo && nd < hi)) nd = 0.5 * (lo + hi);
         const double step = fabs(nd - d);
         d = nd;
-        if ((newton && step <= 1e-8 * d) || step <= 1e-14 * d || step <= 1e-14 * seq / k3 ||
-            hi - lo <= 1e-14 * hi)
-            return d;
+        if (step <= 1e-14 * d || step <= tiny || hi - lo <= 1e-14 * hi) return d;
     }
     flags |= kErrNewton;
     return d;
