@@ -256,7 +256,9 @@ tlsph_status tlsph_set_state(tlsph_ctx *ctx, tlsph_field field, const double *sr
 tlsph_status tlsph_neighbor_count(const tlsph_ctx *ctx, int64_t *nnz);
 
 /* The neighbour list in caller order as CSR with ascending rows:
- * row_ptr (dev, int64[n+1]), col (dev, int32[nnz]).  Errors: BAD_STATE. */
+ * row_ptr (dev, int64[n+1]), col (dev, int32[nnz]).  Writes these arrays
+ * alone, so it may overlap the context's other calls (but a build) on other
+ * streams.  Errors: BAD_STATE. */
 tlsph_status tlsph_get_neighbors(tlsph_ctx *ctx, int64_t *row_ptr, int32_t *col,
                                  hipStream_t stream);
 

@@ -778,7 +778,6 @@ tlsph_status tlsph_build_neighbors(tlsph_ctx* c, const double* X, const double* 
     b.H = 2 * L.n_pow2;
     b.found = at<int32_t>(c, L.halo);
     b.k_cap = L.k_cap;
-    b.part = at<int64_t>(c, L.diag_part);
     HIPCHK(c, launch_build_count(c->st, b, stream));
     alignas(8) int32_t err[8];
     int64_t total_slots = 0;
@@ -1085,7 +1084,7 @@ tlsph_status tlsph_neighbor_count(const tlsph_ctx* c, int64_t* nnz) {
 tlsph_status tlsph_get_neighbors(tlsph_ctx* c, int64_t* row_ptr, int32_t* col, hipStream_t stream) {
     if (!c || !row_ptr || !col) return fail(c, TLSPH_E_INVALID_ARG, "null argument");
     if (!c->built) return fail(c, TLSPH_E_BAD_STATE, "get_neighbors before build");
-    HIPCHK(c, launch_export_neighbors(c->st, row_ptr, col, at<int64_t>(c, c->L.diag_part), stream));
+    HIPCHK(c, launch_export_neighbors(c->st, row_ptr, col, stream));
     return TLSPH_OK;
 }
 

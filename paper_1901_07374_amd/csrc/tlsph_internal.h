@@ -244,7 +244,6 @@ struct BuildBuffers {
     int64_t H;
     int32_t* found;          // [k_cap][n] neighbour lists before they are sliced (the halo lists' place)
     int32_t k_cap;
-    int64_t* part;           // block sums of the scan
 };
 
 hipError_t launch_build_count(DevState& s, const BuildBuffers& b, hipStream_t st);
@@ -272,7 +271,7 @@ hipError_t launch_get_field(const DevState& s, int field, int parity, bool mixed
 hipError_t launch_set_field(const DevState& s, int field, int parity, bool mixed,
                             const double* src, hipStream_t st);
 hipError_t launch_export_neighbors(const DevState& s, int64_t* row_ptr, int32_t* col,
-                                   int64_t* scratch, hipStream_t st);
+                                   hipStream_t st);
 // Two-level fixed-order reductions: chunk partials (seg[q] .. seg[q+1] are the
 // chunks of segment q: specimens first, then boundary groups), then one block
 // per segment.

@@ -467,60 +467,69 @@ __global__ void __launch_bounds__(256) k_count(DevState s, const double* __restr
     }
 }
 
-// In-place inclusive scan of a[0..m): the sums of blocks of kScanB kScanPer
-// values (part), then each block's values from the sum of the parts before it.
+// In-place inclusive scan of a[0..m) with no memory but a itself, so that calls
+// on several streams share nothing: chunks of kScanB kScanPer values, then
+// their last values (the chunks' sums) by one workgroup, then each chunk from
+// the last value of the one before it, which its own workgroup leaves alone.
 constexpr int kScanB = 256, kScanPer = 8;
-__device__ __forceinline__ int64_t block_sum(int64_t v, int64_t* red) {
-    red[threadIdx.x] = v;
-    __syncthreads();
-    for (int w = kScanB / 2; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-        __syncthreads();
-    }
-    const int64_t sum = red[0];
-    __syncthreads();
-    return sum;
-}
-__global__ void __launch_bounds__(kScanB) k_scan_part(const int64_t* __restrict__ a, int64_t m,
-                                                      int64_t* __restrict__ part) {
-    __shared__ int64_t red[kScanB];
-    const int64_t base = (int64_t)blockIdx.x * kScanB * kScanPer;
-    int64_t v = 0;
-    for (int u = 0; u < kScanPer; ++u) {
-        const int64_t q = base + u * kScanB + threadIdx.x;
-        if (q < m) v += a[q];
-    }
-    v = block_sum(v, red);
-    if (threadIdx.x == 0) part[blockIdx.x] = v;
-}
-__global__ void __launch_bounds__(kScanB) k_scan_apply(int64_t* __restrict__ a, int64_t m,
-                                                       const int64_t* __restrict__ part) {
-    __shared__ int64_t red[kScanB];
+constexpr int64_t kScanChunk = kScanB * kScanPer;
+// Inclusive scan of v over the workgroup; total: its sum.
+__device__ __forceinline__ int64_t block_scan(int64_t v, int64_t* red, int64_t* total) {
     const int t = threadIdx.x;
-    int64_t before = 0;
-    for (int64_t q = t; q < (int64_t)blockIdx.x; q += kScanB) before += part[q];
-    before = block_sum(before, red);
-    const int64_t base = (int64_t)blockIdx.x * kScanB * kScanPer;
-    for (int u = 0; u < kScanPer; ++u) {   // kScanB values at a time
-        const int64_t q = base + u * kScanB + t;
-        red[t] = q < m ? a[q] : 0;
+    red[t] = v;
+    __syncthreads();
+    for (int w = 1; w < kScanB; w <<= 1) {
+        const int64_t u = t >= w ? red[t - w] : 0;
         __syncthreads();
-        for (int w = 1; w < kScanB; w <<= 1) {
-            const int64_t v = t >= w ? red[t - w] : 0;
-            __syncthreads();
-            red[t] += v;
-            __syncthreads();
-        }
-        if (q < m) a[q] = before + red[t];
-        before += red[kScanB - 1];
+        red[t] += u;
         __syncthreads();
     }
+    v = red[t];
+    *total = red[kScanB - 1];
+    __syncthreads();
+    return v;
 }
-static hipError_t launch_scan(int64_t* a, int64_t m, int64_t* part, hipStream_t st) {
-    const unsigned blocks = (unsigned)((m + kScanB * kScanPer - 1) / (kScanB * kScanPer));
-    if (blocks == 0) return hipSuccess;
-    k_scan_part<<<blocks, kScanB, 0, st>>>(a, m, part);
-    k_scan_apply<<<blocks, kScanB, 0, st>>>(a, m, part);
+__global__ void __launch_bounds__(kScanB) k_scan_chunks(int64_t* __restrict__ a, int64_t m) {
+    __shared__ int64_t red[kScanB];
+    const int64_t base = (int64_t)blockIdx.x * kScanChunk + (int64_t)threadIdx.x * kScanPer;
+    int64_t v[kScanPer], sum = 0, total;
+#pragma unroll
+    for (int u = 0; u < kScanPer; ++u) {
+        if (base + u < m) sum += a[base + u];
+        v[u] = sum;
+    }
+    const int64_t before = block_scan(sum, red, &total) - sum;
+#pragma unroll
+    for (int u = 0; u < kScanPer; ++u)
+        if (base + u < m) a[base + u] = before + v[u];
+}
+__global__ void __launch_bounds__(kScanB) k_scan_ends(int64_t* __restrict__ a, int64_t m,
+                                                      int64_t chunks) {
+    __shared__ int64_t red[kScanB];
+    int64_t before = 0;
+    for (int64_t c0 = 0; c0 < chunks; c0 += kScanB) {
+        const int64_t c = c0 + threadIdx.x;
+        const int64_t end = (c + 1) * kScanChunk < m ? (c + 1) * kScanChunk : m;
+        int64_t total;
+        const int64_t v = block_scan(c < chunks ? a[end - 1] : 0, red, &total);
+        if (c < chunks) a[end - 1] = before + v;
+        before += total;
+    }
+}
+__global__ void __launch_bounds__(kScanB) k_scan_add(int64_t* __restrict__ a, int64_t m) {
+    const int64_t beg = ((int64_t)blockIdx.x + 1) * kScanChunk;   // (the first chunk is done)
+    const int64_t end = beg + kScanChunk < m ? beg + kScanChunk : m;
+    const int64_t before = a[beg - 1];
+    for (int64_t q = beg + threadIdx.x; q < end - 1; q += kScanB) a[q] += before;
+}
+static hipError_t launch_scan(int64_t* a, int64_t m, hipStream_t st) {
+    const int64_t chunks = (m + kScanChunk - 1) / kScanChunk;
+    if (chunks == 0) return hipSuccess;
+    k_scan_chunks<<<(unsigned)chunks, kScanB, 0, st>>>(a, m);
+    if (chunks > 1) {
+        k_scan_ends<<<1, kScanB, 0, st>>>(a, m, chunks);
+        k_scan_add<<<(unsigned)(chunks - 1), kScanB, 0, st>>>(a, m);
+    }
     return hipGetLastError();
 }
 
@@ -664,7 +673,7 @@ hipError_t launch_build_count(DevState& s, const BuildBuffers& b, hipStream_t st
     k_count<<<gp, T, 0, st>>>(s, b.bbox, b.cell, b.H, b.k_cap,
                               const_cast<int32_t*>(s.nnb), const_cast<int64_t*>(s.slice_ptr),
                               b.found);
-    return launch_scan(const_cast<int64_t*>(s.slice_ptr) + 1, s.np / kSlice, b.part, st);
+    return launch_scan(const_cast<int64_t*>(s.slice_ptr) + 1, s.np / kSlice, st);
 }
 
 // One workgroup per tile of T particles: collect the indices of the tile's
@@ -3153,11 +3162,11 @@ __global__ void k_export_fill(DevState s, const int64_t* __restrict__ row_ptr,
 }
 
 hipError_t launch_export_neighbors(const DevState& s, int64_t* row_ptr, int32_t* col,
-                                   int64_t* part, hipStream_t st) {
+                                   hipStream_t st) {
     const int T = 256;
     const unsigned g = (unsigned)((s.n + T - 1) / T);
     k_export_count<<<g, T, 0, st>>>(s, row_ptr);
-    hipError_t e = launch_scan(row_ptr + 1, s.n, part, st);
+    hipError_t e = launch_scan(row_ptr + 1, s.n, st);
     if (e != hipSuccess) return e;
     k_export_fill<<<g, T, 0, st>>>(s, row_ptr, col);
     return hipGetLastError();

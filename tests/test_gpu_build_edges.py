@@ -54,3 +54,27 @@ def test_lists_at_block_edges(tl, orc, n, groups):
         assert bd[k, 6] == sel.sum()
         if sel.any():
             assert np.allclose(bd[k, 3:6], u[sel].mean(0), rtol=1e-12, atol=1e-18)
+
+
+def test_export_leaves_the_workspace_alone(tl):
+    """The export's scan works in the caller's arrays: nothing of the context
+    changes, so that it may run beside diagnostics or another export."""
+    import torch
+    p = beam(131073, "last")
+    g = tl.Sim(p)
+    rp, col = g.neighbors()
+    ref = g.diagnostics()
+    before = g.ws.clone()
+    g.neighbors()
+    assert torch.equal(g.ws, before)
+    streams = [torch.cuda.Stream() for _ in range(3)]
+    outs = [(torch.empty(p.n + 1, dtype=torch.int64, device="cuda"),
+             torch.empty(len(col), dtype=torch.int32, device="cuda")) for _ in streams]
+    torch.cuda.synchronize()
+    for s, (r, c) in zip(streams, outs):
+        assert tl.lib().tlsph_get_neighbors(g.ctx, r.data_ptr(), c.data_ptr(), s.cuda_stream) == 0
+    got = g.diagnostics()
+    torch.cuda.synchronize()
+    for r, c in outs:
+        assert np.array_equal(r.cpu().numpy(), rp) and np.array_equal(c.cpu().numpy(), col)
+    assert all(np.array_equal(a, b) for a, b in zip(got, ref))
