@@ -305,8 +305,7 @@ tlsph_status contact_rebuild(tlsph_ctx* c, hipStream_t stream) {
     h.gpos = at<D4>(c, L.gpos);
     h.gref = at<D4>(c, L.gref);
     h.H = 2 * L.n_pow2;
-    h.shift = 64;
-    for (int64_t v = h.H; v > 1; v >>= 1) --h.shift;
+    h.shift = table_shift(h.H);
     hipError_t e = launch_contact_build(c->st, c->parity, at<uint64_t>(c, L.keys),
                                         at<int32_t>(c, L.vals), h, at<double>(c, L.cbox), stream);
     if (e != hipSuccess) return hip_fail(c, e, "contact list");

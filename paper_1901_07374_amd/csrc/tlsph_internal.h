@@ -231,6 +231,23 @@ struct CSlot {
     int32_t cnt;
     int32_t start;
 };
+// A cell's home slot in a table of 2^(64 - shift): the top bits of the product,
+// which every bit of the key reaches.  (The bits above 20, as the build took
+// them, leave the specimen out: 20000 specimens of 125 particles shared the
+// slots of one and took 720 ms to build, so 13.)
+__host__ __device__ inline int64_t cell_home(uint64_t key, int shift) {
+    return (int64_t)((key * 0x9e3779b97f4a7c15ull) >> shift);
+}
+inline int table_shift(int64_t slots) {
+    int shift = 64;
+    for (int64_t v = slots; v > 1; v >>= 1) --shift;
+    return shift;
+}
+// The build's cell keys, by coordinates: the curve's key takes a loop per cell.
+__host__ __device__ inline uint64_t grid_key(int sp, int32_t x, int32_t y, int32_t z) {
+    return ((uint64_t)sp << kSpecShift) |
+           ((uint64_t)(((uint32_t)z << kCellBits) | (uint32_t)y) << kCellBits) | (uint32_t)x;
+}
 struct BuildBuffers {
     const double* X_in;      // caller order [3][n]
     const double* V0_in;

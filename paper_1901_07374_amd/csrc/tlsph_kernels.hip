@@ -330,21 +330,13 @@ __global__ void k_spec_ranges(DevSpec* specs, int n_spec, const uint64_t* __rest
 // addressing; H, a power of two, at least twice the particles, so that a
 // search always meets a free slot).
 constexpr uint64_t kNoCell = ~0ull;
-__device__ __forceinline__ int64_t cell_home(uint64_t key, int64_t H) {
-    return (int64_t)((key * 0x9e3779b97f4a7c15ull) >> 20) & (H - 1);
-}
 __global__ void k_cells_clear(CSlot* __restrict__ cell, int64_t H) {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (t < H) cell[t].key = kNoCell;
 }
-// (keyed by the cell's coordinates: the curve's key takes a loop per cell)
-__device__ __forceinline__ uint64_t grid_key(int sp, int32_t x, int32_t y, int32_t z) {
-    return ((uint64_t)sp << kSpecShift) |
-           ((uint64_t)(((uint32_t)z << kCellBits) | (uint32_t)y) << kCellBits) | (uint32_t)x;
-}
 __global__ void k_cells_insert(DevState s, const uint64_t* __restrict__ keys,
                                const double* __restrict__ bbox, CSlot* __restrict__ cell,
-                               int64_t H) {
+                               int64_t H, int shift) {
     const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= s.n || (p > 0 && keys[p - 1] == keys[p])) return;   // the first of its cell
     int64_t end = p + 1;
@@ -354,7 +346,7 @@ __global__ void k_cells_insert(DevState s, const uint64_t* __restrict__ keys,
     int32_t c[3];
     cell_of(bbox + kBBox * sp, x.x, x.y, x.z, c);
     const uint64_t key = grid_key(sp, c[0], c[1], c[2]);
-    for (int64_t h = cell_home(key, H);; h = (h + 1) & (H - 1))
+    for (int64_t h = cell_home(key, shift);; h = (h + 1) & (H - 1))
         if (atomicCAS(reinterpret_cast<unsigned long long*>(&cell[h].key), kNoCell, key) == kNoCell) {
             cell[h].start = (int32_t)p;
             cell[h].cnt = (int32_t)(end - p);
@@ -370,7 +362,8 @@ __global__ void k_cells_insert(DevState s, const uint64_t* __restrict__ keys,
 // of a cell four at a time.
 template <typename F>
 __device__ __forceinline__ int for_neighbours(const DevState& s, const double* bbox,
-                                              const CSlot* cell, int64_t H, int64_t p, F&& visit) {
+                                              const CSlot* cell, int64_t H, int shift, int64_t p,
+                                              F&& visit) {
 #pragma clang fp contract(off)
     const int sp = s.spec[p];
     const DevSpec& P = s.specs[sp];
@@ -393,7 +386,7 @@ __device__ __forceinline__ int for_neighbours(const DevState& s, const double* b
             const int32_t cx = c[0] + e % 3 - 1, cy = c[1] + e / 3 - 1, cz = c[2] + dz;
             in[e] = (uint32_t)cx < kCells && (uint32_t)cy < kCells && (uint32_t)cz < kCells;
             key[e] = in[e] ? grid_key(sp, cx, cy, cz) : grid_key(sp, c[0], c[1], c[2]);
-            h[e] = cell_home(key[e], H);
+            h[e] = cell_home(key[e], shift);
             slot[e] = cell[h[e]];
         }
 #pragma unroll
@@ -440,7 +433,7 @@ __device__ __forceinline__ int for_neighbours(const DevState& s, const double* b
 // for 200k particles, this and k_fill 160 + 10.
 static_assert(kSlice == 64, "a slice is a wave");
 __global__ void __launch_bounds__(256) k_count(DevState s, const double* __restrict__ bbox,
-                                               const CSlot* __restrict__ cell, int64_t H, int k_cap,
+                                               const CSlot* __restrict__ cell, int64_t H, int shift, int k_cap,
                                                int32_t* __restrict__ nnb,
                                                int64_t* __restrict__ slice_ptr,
                                                int32_t* __restrict__ found) {
@@ -448,7 +441,7 @@ __global__ void __launch_bounds__(256) k_count(DevState s, const double* __restr
     if (p >= s.np) return;   // (whole waves: np is a multiple of the slice)
     int cnt = 0;
     if (p < s.n)
-        cnt = for_neighbours(s, bbox, cell, H, p, [&](int k, int32_t q) {
+        cnt = for_neighbours(s, bbox, cell, H, shift, p, [&](int k, int32_t q) {
             if (k < k_cap) found[(int64_t)k * s.n + p] = q;
         });
     nnb[p] = cnt;
@@ -668,9 +661,10 @@ hipError_t launch_build_count(DevState& s, const BuildBuffers& b, hipStream_t st
                                                       b.keys, s.n);
     const unsigned gh = (unsigned)((b.H + T - 1) / T);
     k_cells_clear<<<gh, T, 0, st>>>(b.cell, b.H);
-    k_cells_insert<<<(unsigned)((s.n + T - 1) / T), T, 0, st>>>(s, b.keys, b.bbox, b.cell,
-                                                                        b.H);
-    k_count<<<gp, T, 0, st>>>(s, b.bbox, b.cell, b.H, b.k_cap,
+    const int shift = table_shift(b.H);
+    k_cells_insert<<<(unsigned)((s.n + T - 1) / T), T, 0, st>>>(s, b.keys, b.bbox, b.cell, b.H,
+                                                                shift);
+    k_count<<<gp, T, 0, st>>>(s, b.bbox, b.cell, b.H, shift, b.k_cap,
                               const_cast<int32_t*>(s.nnb), const_cast<int64_t*>(s.slice_ptr),
                               b.found);
     return launch_scan(const_cast<int64_t*>(s.slice_ptr) + 1, s.np / kSlice, st);
@@ -3325,9 +3319,6 @@ __device__ __forceinline__ int64_t cgrid_slot(const CGrid& g, int32_t x, int32_t
 }
 
 // First slot probed for a key (Fibonacci hashing), then linear probing.
-__device__ __forceinline__ int64_t chash_home(const CHash& h, uint64_t key) {
-    return (int64_t)((key * 0x9E3779B97F4A7C15ull) >> h.shift);
-}
 
 __global__ void k_chash_clear(CHash h) {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -3357,7 +3348,7 @@ __global__ void k_chash_insert(DevState s, int par, const double* __restrict__ c
         t = cgrid_slot(G, c[0], c[1], c[2]);
     } else {
         const uint64_t key = ccell_key(c);
-        t = chash_home(h, key);
+        t = cell_home(key, h.shift);
         for (;;) {
             const unsigned long long old =
                 atomicCAS((unsigned long long*)&h.slot[t].key, ~0ull, (unsigned long long)key);
@@ -3521,7 +3512,7 @@ __device__ void cfill_hashed(const DevState& s, const CHash& h, const int32_t* m
         for (int k = 0; k < 3; ++k) {
             const int32_t cc[3] = {c[0] + k - 1, cy, cz};
             key[k] = (cc[0] >= 0 && cc[0] < kAxis) ? ccell_key(cc) : ~0ull;
-            t[k] = chash_home(h, key[k]);
+            t[k] = cell_home(key[k], h.shift);
             r[k] = h.slot[t[k]];
         }
 #pragma unroll
