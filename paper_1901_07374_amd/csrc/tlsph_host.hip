@@ -145,6 +145,8 @@ Layout make_layout(int64_t n, int32_t n_spec, int32_t n_bc, int32_t k_cap, bool 
 
 bool finite_pos(double x) { return isfinite(x) && x > 0.0; }
 
+int64_t diag_chunks(int64_t m) { return m > 0 ? (m + kDiagChunk - 1) / kDiagChunk : 1; }
+
 }  // namespace
 
 struct tlsph_ctx {
@@ -740,6 +742,14 @@ tlsph_status tlsph_create(int64_t n, int32_t n_spec, const int64_t* spec_offsets
     if (e == hipSuccess)
         e = hipMemcpyAsync(c->ws + L.spec_off, c->spec_off.data(), (n_spec + 1) * sizeof(int64_t),
                            hipMemcpyHostToDevice, stream);
+    // the diagnostics chunks of each specimen (the build uses them too)
+    c->diag_seg_host.assign((size_t)n_spec + n_bc + 1, 0);
+    for (int32_t q = 0; q < n_spec; ++q)
+        c->diag_seg_host[q + 1] = c->diag_seg_host[q] + diag_chunks(spec_offsets[q + 1] - spec_offsets[q]);
+    c->diag_chunks_spec = c->diag_seg_host[n_spec];
+    if (e == hipSuccess)
+        e = hipMemcpyAsync(c->ws + L.diag_seg, c->diag_seg_host.data(),
+                           (n_spec + 1) * sizeof(int64_t), hipMemcpyHostToDevice, stream);
     if (e != hipSuccess) {
         delete c;
         return TLSPH_E_HIP;
@@ -769,6 +779,8 @@ tlsph_status tlsph_build_neighbors(tlsph_ctx* c, const double* X, const double* 
     b.V0_in = V0;
     b.bc_in = bc_group;
     b.spec_off = at<int64_t>(c, L.spec_off);
+    b.seg = at<int64_t>(c, L.diag_seg);
+    b.chunks = c->diag_chunks_spec;
     b.bbox = at<double>(c, L.bbox);
     b.keys = at<uint64_t>(c, L.keys);
     b.vals = at<int32_t>(c, L.vals);
@@ -852,21 +864,16 @@ tlsph_status tlsph_build_neighbors(tlsph_ctx* c, const double* X, const double* 
                                  hipMemcpyDeviceToHost, stream));
         HIPCHK(c, hipStreamSynchronize(stream));
     }
-    // diagnostics segments: chunks of each specimen, then of each group
+    // diagnostics segments: the chunks of each group after those of the specimens
     {
         std::vector<int64_t>& seg = c->diag_seg_host;
-        seg.assign((size_t)L.n_spec + L.n_bc + 1, 0);
-        auto chunks = [](int64_t m) { return m > 0 ? (m + kDiagChunk - 1) / kDiagChunk : 1; };
-        for (int32_t q = 0; q < L.n_spec; ++q)
-            seg[q + 1] = seg[q] + chunks(c->spec_off[q + 1] - c->spec_off[q]);
         for (int32_t g = 0; g < L.n_bc; ++g)
-            seg[L.n_spec + g + 1] = seg[L.n_spec + g] + chunks(bptr[g + 1] - bptr[g]);
+            seg[L.n_spec + g + 1] = seg[L.n_spec + g] + diag_chunks(bptr[g + 1] - bptr[g]);
         if (seg.back() > L.diag_chunk_cap)
             return fail(c, TLSPH_E_HIP, "diagnostics chunk table exceeds its capacity");
         // (the host table lives in the context, so the copy may complete later)
         HIPCHK(c, hipMemcpyAsync(c->ws + L.diag_seg, seg.data(), seg.size() * 8,
                                  hipMemcpyHostToDevice, stream));
-        c->diag_chunks_spec = seg[L.n_spec];
         c->diag_chunks_all = seg.back();
     }
     c->nnz = pairs;

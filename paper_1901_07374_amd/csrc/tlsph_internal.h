@@ -253,6 +253,8 @@ struct BuildBuffers {
     const double* V0_in;
     const int32_t* bc_in;
     const int64_t* spec_off; // device copy [n_spec + 1]
+    const int64_t* seg;      // [n_spec + 1] first diagnostics chunk of each specimen
+    int64_t chunks;          // their number
     double* bbox;            // [n_spec][6]
     uint64_t* keys;          // [n_pow2]
     int32_t* vals;           // [n_pow2]

@@ -63,11 +63,14 @@ __device__ __forceinline__ uint64_t cell_key(uint32_t x, uint32_t y, uint32_t z)
 // specimen's h, or with graded spacing the largest support h_per_spacing
 // (max V0)^(1/3), each a hair larger so that pairs closer than the support
 // never sit two cells apart after rounding.
-// Found by all compute units: chunks of a specimen reduce in LDS and meet in
-// atomics on the extrema as ordered integers, kept in the record itself (one
-// workgroup per specimen took 281 us for 200k particles, now 11).
+// Found by all compute units: each specimen's chunks (those of the diagnostics,
+// at most kBBoxParts workgroups of them) reduce in LDS and meet in atomics on the
+// extrema as ordered integers, kept in the record itself.  One workgroup per
+// specimen took 281 us for 200k particles, this 11; with a grid row per specimen
+// and columns for the chunks of them all, nearly all empty, 70000 specimens of
+// eight took 33 ms to build, so 1.1.
 constexpr int kBBox = 8;
-constexpr int kBBoxChunk = 2048;   // particles per workgroup, at least
+constexpr int kBBoxParts = 256;
 __device__ __forceinline__ unsigned long long ordered_bits(double x) {
     const unsigned long long b = (unsigned long long)__double_as_longlong(x);
     return b ^ ((b >> 63) ? ~0ull : 1ull << 63);
@@ -83,12 +86,23 @@ __global__ void k_bbox_clear(unsigned long long* __restrict__ bits, int n_spec) 
 __global__ void __launch_bounds__(256) k_bbox(const double* __restrict__ X,
                                               const double* __restrict__ V0, int64_t n,
                                               const int64_t* __restrict__ off,
+                                              const int64_t* __restrict__ seg, int n_spec,
                                               unsigned long long* __restrict__ bits) {
     __shared__ double red[7][256];
-    const int s = blockIdx.y;
+    // the specimen of chunk b: every one has a chunk, so it lies within the
+    // chunks beyond one each below b
+    const int64_t b = blockIdx.x, more = seg[n_spec] - n_spec;
+    int64_t s = b > more ? b - more : 0, top = b < n_spec ? b : n_spec - 1;
+    while (s < top) {
+        const int64_t mid = (s + top + 1) >> 1;
+        if (seg[mid] <= b) s = mid; else top = mid - 1;
+    }
+    const int64_t all = seg[s + 1] - seg[s], parts = all < kBBoxParts ? all : kBBoxParts;
+    if (b - seg[s] >= parts) return;
+    const int64_t last = off[s + 1], beg = off[s] + (b - seg[s]) * 256;
+    const int64_t m = last - beg;   // (lanes past the specimen's end hold nothing)
     double lo[3] = {1e300, 1e300, 1e300}, hi[3] = {-1e300, -1e300, -1e300}, vmax = 0.0;
-    for (int64_t i = off[s] + (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < off[s + 1];
-         i += (int64_t)gridDim.x * blockDim.x) {
+    for (int64_t i = beg + threadIdx.x; i < last; i += parts * 256) {
         for (int c = 0; c < 3; ++c) {
             const double x = X[c * n + i];
             lo[c] = x < lo[c] ? x : lo[c];
@@ -102,7 +116,9 @@ __global__ void __launch_bounds__(256) k_bbox(const double* __restrict__ X,
     }
     red[6][threadIdx.x] = vmax;
     __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
+    int w = 128;
+    while (w >= m && w > 0) w >>= 1;
+    for (; w > 0; w >>= 1) {
         if ((int)threadIdx.x < w) {
             for (int c = 0; c < 3; ++c) {
                 red[c][threadIdx.x] = fmin(red[c][threadIdx.x], red[c][threadIdx.x + w]);
@@ -642,10 +658,9 @@ __global__ void k_init(DevState s) {
 hipError_t launch_build_count(DevState& s, const BuildBuffers& b, hipStream_t st) {
     const int T = 256;
     unsigned long long* bits = reinterpret_cast<unsigned long long*>(b.bbox);
-    const int64_t chunks = (s.n + kBBoxChunk - 1) / kBBoxChunk;
-    const dim3 bb((unsigned)(chunks < 256 ? chunks : 256), (unsigned)s.n_spec);
     k_bbox_clear<<<(s.n_spec * kBBox + T - 1) / T, T, 0, st>>>(bits, s.n_spec);
-    k_bbox<<<bb, 256, 0, st>>>(b.X_in, b.V0_in, s.n, b.spec_off, bits);
+    k_bbox<<<(unsigned)b.chunks, 256, 0, st>>>(b.X_in, b.V0_in, s.n, b.spec_off, b.seg, s.n_spec,
+                                               bits);
     k_bbox_final<<<(s.n_spec + T - 1) / T, T, 0, st>>>(b.bbox, s.n_spec, s.specs);
     k_keys<<<(unsigned)((b.n_pow2 + T - 1) / T), T, 0, st>>>(b.X_in, s.n, b.n_pow2, b.spec_off,
                                                              s.n_spec, b.bbox, b.keys, b.vals,

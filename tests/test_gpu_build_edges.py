@@ -78,3 +78,23 @@ def test_export_leaves_the_workspace_alone(tl):
     for r, c in outs:
         assert np.array_equal(r.cpu().numpy(), rp) and np.array_equal(c.cpu().numpy(), col)
     assert all(np.array_equal(a, b) for a, b in zip(got, ref))
+
+
+def test_many_specimens(tl):
+    """More specimens than a grid may have rows: cubes of eight particles each,
+    against their pair distances."""
+    m, dx = 70000, 1e-3
+    rng = np.random.default_rng(7)
+    corner = np.array([[q & 1, q >> 1 & 1, q >> 2] for q in range(8)]) * dx
+    X = corner + rng.uniform(-0.05 * dx, 0.05 * dx, (m, 8, 3))
+    mat = I.material(dx, I.DMG_NONE)
+    p = I.Problem("cubes", X.reshape(-1, 3), np.full(8 * m, dx ** 3), 8 * np.arange(m + 1),
+                  [mat] * m, np.full(8 * m, -1, np.int32), [], np.zeros((8 * m, 3)), steps=1,
+                  dx=np.full(m, dx))
+    rp, col = tl.Sim(p, k_cap=8).neighbors()
+    d = X[:, None] - X[:, :, None]
+    near = (d[..., 0] * d[..., 0] + d[..., 1] * d[..., 1] + d[..., 2] * d[..., 2]
+            < mat["h"] * mat["h"]) & ~np.eye(8, dtype=bool)
+    s, _, j = np.nonzero(near)
+    assert np.array_equal(np.diff(rp), near.sum(2).ravel())
+    assert np.array_equal(col, 8 * s + j)
