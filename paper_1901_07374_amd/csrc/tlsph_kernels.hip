@@ -1337,7 +1337,8 @@ struct FinishIn {
 };
 // The velocity ramp 1 - exp(-t / tau) of the boundary group and specimen a wave
 // met last (the same for every particle of a launch: the pipelined pass's waves
-// finish many tiles, mostly of one group).
+// finish many tiles, mostly of one group).  Scalars: set where the whole wave
+// goes (meet_group), never in a turn of some of its lanes.
 struct Ramp {
     int32_t group = -1, sp = -1;
     double value = 0.0;
@@ -1353,6 +1354,23 @@ __device__ __forceinline__ double uniform(double x) {
     const unsigned lo = __builtin_amdgcn_readfirstlane((int)(b & 0xffffffffll));
     const unsigned hi = __builtin_amdgcn_readfirstlane((int)(b >> 32));
     return __longlong_as_double(((long long)hi << 32) | lo);
+}
+
+__device__ __forceinline__ double ramp_value(const DevState& s, const DevBC& B, int sp, double dt) {
+    const double th = s.t[sp] + 0.5 * dt;
+    return B.tau > 0.0 ? 1.0 - exp(-th / B.tau) : 1.0;
+}
+// The ramp of the first lane of the wave that has a boundary group (-1: none),
+// ahead of the lanes' turns in force_finish.  Every lane of the wave comes here.
+__device__ __forceinline__ void meet_group(const DevState& s, int sp_lane, int bc_lane, Ramp& ramp) {
+    const uint64_t with = __ballot(bc_lane >= 0);
+    if (with == 0) return;
+    const int l = __ffsll((unsigned long long)with) - 1;
+    const int g = __builtin_amdgcn_readlane(bc_lane, l), sp = __builtin_amdgcn_readlane(sp_lane, l);
+    if (g == ramp.group && sp == ramp.sp) return;
+    ramp.group = g;
+    ramp.sp = sp;
+    ramp.value = uniform(ramp_value(s, s.bcs[g], sp, s.specs[sp].dt));
 }
 
 // What the finish needs of the wave's first specimen, and its first boundary
@@ -1374,11 +1392,9 @@ __device__ __forceinline__ Met meet(const DevState& s, int sp_lane, int bc_lane,
     if (with) {
         const int g = __builtin_amdgcn_readlane(bc_lane, __ffsll((unsigned long long)with) - 1);
         const DevBC& B = s.bcs[g];
-        const double th = s.t[sp] + 0.5 * m.dt;
-        const double r = B.tau > 0.0 ? 1.0 - exp(-th / B.tau) : 1.0;
         ramp.group = g;
         ramp.sp = sp;
-        ramp.value = uniform(r);
+        ramp.value = uniform(ramp_value(s, B, sp, m.dt));
         asm volatile("" ::"s"(B.mask), "s"(B.v_max[0]), "s"(B.grad[0]), "s"(B.grad[8]));
     }
     return m;
@@ -1390,13 +1406,16 @@ __device__ __forceinline__ Met meet(const DevState& s, int sp_lane, int bc_lane,
 // it (m = rho0 V_i).  The lanes of a wave take turns by specimen, and within
 // it by boundary group (one turn each unless the wave straddles two), so that
 // both records arrive by scalar loads, which the CU's scalar cache keeps: per
-// lane they would be two more dependent trips to memory at the end of a tile.
+// lane they would be two more dependent trips to memory at the end of a tile.  A
+// turn leaves nothing behind but its stores: a scalar set in it and read after
+// the turns could be another turn's.
 // kTwo: two adjacent lanes (sub 0, 1) hold the particle's sums and both come
 // here; each stores half of every record, so that a wave's stores are contiguous.
 template <typename R, bool kVarH = false, bool kTwo = false>
 __device__ __forceinline__ void force_finish(const DevState& s, int64_t i, int par, int sp_lane,
                                              const LRecB<R>& ni, const ForceAcc<R>& A,
-                                             const FinishIn& fin, Ramp& ramp, int sub = 0,
+                                             const FinishIn& fin, const Ramp* ramp = nullptr,
+                                             int sub = 0,
                                              const Met* met = nullptr) {
     const int64_t np = s.np;
     for (;;) {
@@ -1439,18 +1458,13 @@ __device__ __forceinline__ void force_finish(const DevState& s, int64_t i, int p
                 const int gw = __builtin_amdgcn_readfirstlane(grp);
                 if (gw != grp) continue;
                 const DevBC& B = s.bcs[gw];
-                if (gw != ramp.group || sp != ramp.sp) {
-                    const double th = s.t[sp] + 0.5 * dt;
-                    const double r = B.tau > 0.0 ? 1.0 - exp(-th / B.tau) : 1.0;
-                    ramp.group = gw;
-                    ramp.sp = sp;
-                    ramp.value = uniform(r);
-                }
+                const bool met_it = ramp && gw == ramp->group && sp == ramp->sp;
+                const double r = met_it ? ramp->value : ramp_value(s, B, sp, dt);
 #pragma unroll
                 for (int c = 0; c < 3; ++c)
                     if (B.mask & (1 << c))
-                        v[c] = B.v_max[c] * ramp.value + (B.grad[3 * c] * xi + B.grad[3 * c + 1] * yi +
-                                                    B.grad[3 * c + 2] * zi);
+                        v[c] = B.v_max[c] * r + (B.grad[3 * c] * xi + B.grad[3 * c + 1] * yi +
+                                                 B.grad[3 * c + 2] * zi);
                 break;
             }
         }
@@ -1539,8 +1553,8 @@ k_pass_b(DevState s, int par) {
     // keeps the load here) rather than keep it in registers through the loop
     asm volatile("" ::: "memory");
     if (live && sub == 0)
-        force_finish<R, kVarH>(s, i, par, sp, make_recb<R>(XV[i], GQ[i], GH[i], Uc[i]), A, fin, ramp,
-                               0, &met);
+        force_finish<R, kVarH>(s, i, par, sp, make_recb<R>(XV[i], GQ[i], GH[i], Uc[i]), A, fin,
+                               &ramp, 0, &met);
 }
 
 // 16 bytes per lane from global memory straight into LDS: lane l of the wave
@@ -1826,8 +1840,7 @@ __device__ __forceinline__ void pass_b_sweeps(const DevState& s, int par) {
         ni.ux = a.x; ni.uy = a.y; ni.uz = L.uz[pl].x;
 #pragma unroll
         for (int k = 0; k < 9; ++k) ni.q[k] = q.q[k];
-        Ramp ramp;
-        force_finish<R, kVarH>(s, i, par, sp, ni, A, fin, ramp);
+        force_finish<R, kVarH>(s, i, par, sp, ni, A, fin);
     }
 }
 
@@ -2145,6 +2158,7 @@ __device__ __forceinline__ void pass_b_pipe(const DevState& s, int par) {
             A.st = combine_partials<S>(B);
         }
         const bool stores = in && !frozen(s, cur.sp);
+        meet_group(s, cur.sp, stores ? fin.bc : -1, ramp);
         if (stores) {
             LRecB<R> ni;
             const LdsGQ<R> q = L.gq[pl];
@@ -2152,7 +2166,7 @@ __device__ __forceinline__ void pass_b_pipe(const DevState& s, int par) {
             ni.ux = uxyi.x; ni.uy = uxyi.y; ni.uz = uzi;
 #pragma unroll
             for (int k = 0; k < 9; ++k) ni.q[k] = q.q[k];
-            force_finish<R, false, true>(s, i, par, cur.sp, ni, A, fin, ramp, sub);
+            force_finish<R, false, true>(s, i, par, cur.sp, ni, A, fin, &ramp, sub);
         }
         if (next < 0) return;
         // the next tile's records have arrived (the finish's two stores, which
@@ -2391,10 +2405,9 @@ k_pass_b_one(DevState s, int par) {
     // barrier above, so a compiler barrier suffices: waves go on to their
     // finish as their own sums end)
     asm volatile("" ::: "memory");
-    Ramp ramp;
     if (in && sub == 0)
         force_finish<R, kVarH>(s, i, par, sp, LdsOne<R>::get(L, M, pl), A,
-                               kEarly ? fin_early : finish_in(s, ii, XV[ii].w), ramp);
+                               kEarly ? fin_early : finish_in(s, ii, XV[ii].w));
 }
 
 // The same in the forms that stage by asynchronous copies: pipelined with two

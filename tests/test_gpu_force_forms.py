@@ -78,3 +78,31 @@ def test_forms_are_bitwise_the_unstaged_pass(tl, problem, precision, lanes, tile
     assert inf["lds_bytes"] % per_slot == 0 and inf["lds_bytes"] > tile * per_slot
     for k in KEYS:
         assert np.array_equal(outs[0][k], outs[1][k]), k
+
+
+@pytest.mark.parametrize("precision,tile", [("fp64", 193), ("fp64", 208), ("mixed", 128)])
+def test_groups_of_several_specimens_in_a_wave(tl, precision, tile):
+    """Specimens whose ramps differ (time steps, time constants), and whose first
+    particles are in groups, so that a wave of the pipelined pass holds lanes of
+    two specimens with groups of both."""
+    p = I.bar_batch(n_spec=3, counts=(90000, 70000, 80000))
+    mats = [dict(m, dt=m["dt"] * f) for m, f in zip(p.materials, (1.0, 0.9, 0.8))]
+    groups = [dict(g, tau=1e-3 * (1 + k)) for k, g in enumerate(p.bc_groups)]
+    bc = p.bc_group.copy()
+    for q in range(3):   # every third particle, alternating between the specimen's groups
+        i = np.arange(p.spec_offsets[q], p.spec_offsets[q + 1], 3)
+        bc[i] = 2 * q + (i % 2)
+    p = I.Problem(p.name, p.X, p.V0, p.spec_offsets, mats, bc, groups, p.v_init, p.steps, p.dx)
+    st = I.random_state(p, seed=13, v_scale=1.0, u_scale=1e-7)
+    outs = []
+    for shape in ((False, 4, 256, 256, 0), (True, 2, 256, 256, tile)):
+        g = tl.Sim(p, precision=tl.FP64 if precision == "fp64" else tl.MIXED, k_cap=32)
+        g.set_launch_shape(*shape)
+        g.set_state(st)
+        g.step(3)
+        outs.append({k: g.get(k) for k in KEYS if k != "force"})
+        inf = g.info()
+    print(precision, tile, p.n, inf, flush=True)
+    assert inf["lds_bytes"] % BYTES["pipe"][precision == "mixed"] == 0
+    for k in outs[0]:
+        assert np.array_equal(outs[0][k], outs[1][k]), k
