@@ -1239,10 +1239,9 @@ __device__ __forceinline__ Slots<S> load_slots(const uint32_t* __restrict__ pslo
 // every S rounds identically.  All lanes of the wave must call this (the
 // partials are exchanged across lanes); lanes without a particle pass cnt = 0.
 // Indices run one group of kSub ahead of the arithmetic.
-// between() runs while the first group's records travel.
-template <typename R, int S, bool kVarH = false, typename IdxOf, typename RecOf, typename Between>
+template <typename R, int S, bool kVarH = false, typename IdxOf, typename RecOf>
 __device__ __forceinline__ ForceAcc<R> pair_sums(const LRecB<R>& ni, int cnt, int sub, R inv_h,
-                                                 IdxOf idx, RecOf rec, Between between) {
+                                                 IdxOf idx, RecOf rec) {
     static_assert(kSub == 4 && (S == 1 || S == 2 || S == 4), "canonical order has 4 partials");
     constexpr int NP = kSub / S;
     ForceAcc<R> A[NP];
@@ -1253,21 +1252,10 @@ __device__ __forceinline__ ForceAcc<R> pair_sums(const LRecB<R>& ni, int cnt, in
         first[t] = idx(k < cnt ? k : 0);
         q[t] = idx(kSub + k < cnt ? kSub + k : 0);
     }
-    if constexpr (NP <= 2) {
-        LRecB<R> nj[NP];
-#pragma unroll
-        for (int t = 0; t < NP; ++t) nj[t] = rec(cnt > 0 ? first[t] : 0);
-        between();
+    if (0 < cnt) {
 #pragma unroll
         for (int t = 0; t < NP; ++t)
-            force_pair<R, kVarH>(ni, nj[t], inv_h, A[t], sub + S * t < cnt);
-    } else {
-        between();
-        if (0 < cnt) {
-#pragma unroll
-            for (int t = 0; t < NP; ++t)
-                force_pair<R, kVarH>(ni, rec(first[t]), inv_h, A[t], sub + S * t < cnt);
-        }
+            force_pair<R, kVarH>(ni, rec(first[t]), inv_h, A[t], sub + S * t < cnt);
     }
     for (int k0 = kSub; k0 < cnt; k0 += kSub) {
         int cur[NP];
@@ -1356,10 +1344,106 @@ __device__ __forceinline__ double uniform(double x) {
     return __longlong_as_double(((long long)hi << 32) | lo);
 }
 
+// The specimen's constants that the finish needs (graded spacing: the pair
+// sums carry the kernel's constant factors).
+struct FinishSpec {
+    double ck, hgk, dt, dt_rho0;
+    int32_t wall;
+};
+template <bool kVarH>
+__device__ __forceinline__ FinishSpec finish_spec(const DevSpec& P) {
+    return FinishSpec{kVarH ? 1.0 : P.grad_k, kVarH ? -P.hg_alpha * P.E : P.hg_k, P.dt, P.dt_rho0,
+                      P.has_wall};
+}
 __device__ __forceinline__ double ramp_value(const DevState& s, const DevBC& B, int sp, double dt) {
     const double th = s.t[sp] + 0.5 * dt;
     return B.tau > 0.0 ? 1.0 - exp(-th / B.tau) : 1.0;
 }
+__device__ __forceinline__ void prescribe(const DevBC& B, double ramp, double xi, double yi,
+                                          double zi, double v[3]) {
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+        if (B.mask & (1 << c))
+            v[c] = B.v_max[c] * ramp +
+                   (B.grad[3 * c] * xi + B.grad[3 * c + 1] * yi + B.grad[3 * c + 2] * zi);
+}
+
+// Nodal force, kick, prescribed velocities (the caller's: by lane, or by wave),
+// failed particles at rest, drift, rigid wall; stores v, V0 (1 - D), u^{n+1} and
+// (for groups) the force.  The force per unit volume f / V_i is formed first:
+// the kick is dt / rho0 times it (m = rho0 V_i).
+// kTwo: two adjacent lanes (sub 0, 1) hold the particle's sums and both come
+// here; each stores half of every record, so that a wave's stores are contiguous.
+template <typename R, bool kTwo, typename Prescribe>
+__device__ __forceinline__ void finish_particle(const DevState& s, int64_t i, int par, int sp,
+                                                const DevSpec& P, const FinishSpec& c,
+                                                const LRecB<R>& ni, const ForceAcc<R>& A,
+                                                const FinishIn& fin, int sub, Prescribe prescribed) {
+    const int64_t np = s.np;
+    const double Di = fin.D;
+    const R omDi = R(1.0 - Di);
+    const R ck = R(c.ck);
+    const R hgk = R(c.hgk) * omDi;
+    const double Vi = fin.V;
+    const StressAcc<R>& a = A.st;
+    const HgAcc<R>& g = A.hg;
+    double fv0 = double(ck * (ni.q[0] * a.a0 + ni.q[1] * a.a1 + ni.q[2] * a.a2 + omDi * a.b0) + hgk * g.g0);
+    double fv1 = double(ck * (ni.q[3] * a.a0 + ni.q[4] * a.a1 + ni.q[5] * a.a2 + omDi * a.b1) + hgk * g.g1);
+    double fv2 = double(ck * (ni.q[6] * a.a0 + ni.q[7] * a.a1 + ni.q[8] * a.a2 + omDi * a.b2) + hgk * g.g2);
+    if (s.av) {   // the artificial viscous force of the last deformation pass
+        const double iv = rcp_nr(Vi);
+        fv0 += s.fvisc[i] * iv;
+        fv1 += s.fvisc[np + i] * iv;
+        fv2 += s.fvisc[2 * np + i] * iv;
+    }
+    if (s.contact) {   // penalty contact with the listed candidates
+        double fc[3];
+        contact_force(s, i, par, sp, ni.x + ni.ux, ni.y + ni.uy, ni.z + ni.uz, Di, fc);
+        const double iv = rcp_nr(Vi);
+        fv0 += fc[0] * iv;
+        fv1 += fc[1] * iv;
+        fv2 += fc[2] * iv;
+    }
+    const double dt = c.dt;
+    double v[3] = {fin.vx + c.dt_rho0 * fv0, fin.vy + c.dt_rho0 * fv1, fin.vz + c.dt_rho0 * fv2};
+    const double xi = ni.x, yi = ni.y, zi = ni.z;
+    if (fin.bc >= 0) prescribed(dt, xi, yi, zi, v);
+    if (Di >= 1.0) v[0] = v[1] = v[2] = 0.0;
+    double un[3] = {ni.ux + dt * v[0], ni.uy + dt * v[1], ni.uz + dt * v[2]};
+    if (c.wall) {
+        const double xw[3] = {xi + un[0], yi + un[1], zi + un[2]};
+        const double dn = xw[0] * P.wall_n[0] + xw[1] * P.wall_n[1] + xw[2] * P.wall_n[2] - P.wall_d;
+        if (dn < 0.0) {
+            un[0] = (xw[0] - dn * P.wall_n[0]) - xi;
+            un[1] = (xw[1] - dn * P.wall_n[1]) - yi;
+            un[2] = (xw[2] - dn * P.wall_n[2]) - zi;
+            const double vn = v[0] * P.wall_n[0] + v[1] * P.wall_n[1] + v[2] * P.wall_n[2];
+            if (vn < 0.0) {
+                v[0] -= vn * P.wall_n[0];
+                v[1] -= vn * P.wall_n[1];
+                v[2] -= vn * P.wall_n[2];
+            }
+        }
+    }
+    const double w = Vi * (1.0 - Di);
+    const bool keep = (s.flags & kFlagStoreForce) || fin.bc >= 0;
+    if constexpr (kTwo) {
+        reinterpret_cast<double2*>(s.VW)[2 * i + sub] = sub ? double2{v[2], w} : double2{v[0], v[1]};
+        reinterpret_cast<double2*>(s.U[par ^ 1])[2 * i + sub] =
+            sub ? double2{un[2], 0.0} : double2{un[0], un[1]};
+        if (keep) {
+            s.force[sub * np + i] = Vi * (sub ? fv1 : fv0);
+            if (!sub) s.force[2 * np + i] = Vi * fv2;
+        }
+    } else {
+        s.VW[i] = D4{v[0], v[1], v[2], w};
+        s.U[par ^ 1][i] = D4{un[0], un[1], un[2], 0.0};
+        if (keep) {
+            s.force[i] = Vi * fv0; s.force[np + i] = Vi * fv1; s.force[2 * np + i] = Vi * fv2;
+        }
+    }
+}
+
 // The ramp of the first lane of the wave that has a boundary group (-1: none),
 // ahead of the lanes' turns in force_finish.  Every lane of the wave comes here.
 __device__ __forceinline__ void meet_group(const DevState& s, int sp_lane, int bc_lane, Ramp& ramp) {
@@ -1373,135 +1457,34 @@ __device__ __forceinline__ void meet_group(const DevState& s, int sp_lane, int b
     ramp.value = uniform(ramp_value(s, s.bcs[g], sp, s.specs[sp].dt));
 }
 
-// What the finish needs of the wave's first specimen, and its first boundary
-// group's ramp, ahead of the pair sums (a kernel of few waves has nothing else to
-// spend their latency on: 1.2k particles, unstaged, four lanes, 10.9 us
-// a pass without, 9.6 with).
-struct Met {
-    int32_t sp, has_wall;
-    double ck, hgk, dt, dt_rho0;
-};
-template <bool kVarH>
-__device__ __forceinline__ Met meet(const DevState& s, int sp_lane, int bc_lane, Ramp& ramp) {
-    const int sp = __builtin_amdgcn_readfirstlane(sp_lane);
-    const DevSpec& P = s.specs[sp];
-    const Met m{sp, P.has_wall, kVarH ? 1.0 : P.grad_k, kVarH ? -P.hg_alpha * P.E : P.hg_k, P.dt,
-                P.dt_rho0};
-    asm volatile("" ::"s"(m.ck), "s"(m.hgk), "s"(m.dt), "s"(m.dt_rho0), "s"(m.has_wall));
-    const uint64_t with = __ballot(bc_lane >= 0);
-    if (with) {
-        const int g = __builtin_amdgcn_readlane(bc_lane, __ffsll((unsigned long long)with) - 1);
-        const DevBC& B = s.bcs[g];
-        ramp.group = g;
-        ramp.sp = sp;
-        ramp.value = uniform(ramp_value(s, B, sp, m.dt));
-        asm volatile("" ::"s"(B.mask), "s"(B.v_max[0]), "s"(B.grad[0]), "s"(B.grad[8]));
-    }
-    return m;
-}
-
-// Nodal force, kick, prescribed velocities, failed particles at rest, drift,
-// rigid wall; stores v, V0 (1 - D), u^{n+1} and (for groups) the force.  The
-// force per unit volume f / V_i is formed first: the kick is dt / rho0 times
-// it (m = rho0 V_i).  The lanes of a wave take turns by specimen, and within
-// it by boundary group (one turn each unless the wave straddles two), so that
-// both records arrive by scalar loads, which the CU's scalar cache keeps: per
-// lane they would be two more dependent trips to memory at the end of a tile.  A
-// turn leaves nothing behind but its stores: a scalar set in it and read after
-// the turns could be another turn's.
-// kTwo: two adjacent lanes (sub 0, 1) hold the particle's sums and both come
-// here; each stores half of every record, so that a wave's stores are contiguous.
+// The finish of the staged forms.  The lanes of a wave take turns by specimen,
+// and within it by boundary group (one turn each unless the wave straddles two),
+// so that both records arrive by scalar loads, which the CU's scalar cache
+// keeps: per lane they would be two more dependent trips to memory at the end
+// of a tile.  A turn leaves nothing behind but its stores: a scalar set in it
+// and read after the turns could be another turn's.
 template <typename R, bool kVarH = false, bool kTwo = false>
 __device__ __forceinline__ void force_finish(const DevState& s, int64_t i, int par, int sp_lane,
                                              const LRecB<R>& ni, const ForceAcc<R>& A,
                                              const FinishIn& fin, const Ramp* ramp = nullptr,
-                                             int sub = 0,
-                                             const Met* met = nullptr) {
-    const int64_t np = s.np;
+                                             int sub = 0) {
     for (;;) {
         const int sp = __builtin_amdgcn_readfirstlane(sp_lane);
         if (sp != sp_lane) continue;
         if (frozen(s, sp)) return;
         const DevSpec& P = s.specs[sp];
-        const double Di = fin.D;
-        const R omDi = R(1.0 - Di);
-        // (graded spacing: the pair sums carry the kernel's constant factors)
-        const bool known = met && met->sp == sp;
-        const R ck = R(known ? met->ck : kVarH ? 1.0 : P.grad_k);
-        const R hgk = R(known ? met->hgk : kVarH ? -P.hg_alpha * P.E : P.hg_k) * omDi;
-        const double Vi = fin.V;
-        const StressAcc<R>& a = A.st;
-        const HgAcc<R>& g = A.hg;
-        double fv0 = double(ck * (ni.q[0] * a.a0 + ni.q[1] * a.a1 + ni.q[2] * a.a2 + omDi * a.b0) + hgk * g.g0);
-        double fv1 = double(ck * (ni.q[3] * a.a0 + ni.q[4] * a.a1 + ni.q[5] * a.a2 + omDi * a.b1) + hgk * g.g1);
-        double fv2 = double(ck * (ni.q[6] * a.a0 + ni.q[7] * a.a1 + ni.q[8] * a.a2 + omDi * a.b2) + hgk * g.g2);
-        if (s.av) {   // the artificial viscous force of the last deformation pass
-            const double iv = rcp_nr(Vi);
-            fv0 += s.fvisc[i] * iv;
-            fv1 += s.fvisc[np + i] * iv;
-            fv2 += s.fvisc[2 * np + i] * iv;
-        }
-        if (s.contact) {   // penalty contact with the listed candidates
-            double fc[3];
-            contact_force(s, i, par, sp, ni.x + ni.ux, ni.y + ni.uy, ni.z + ni.uz, Di, fc);
-            const double iv = rcp_nr(Vi);
-            fv0 += fc[0] * iv;
-            fv1 += fc[1] * iv;
-            fv2 += fc[2] * iv;
-        }
-        const double dt = known ? met->dt : P.dt, dt_rho0 = known ? met->dt_rho0 : P.dt_rho0;
-        double v[3] = {fin.vx + dt_rho0 * fv0, fin.vy + dt_rho0 * fv1, fin.vz + dt_rho0 * fv2};
-        const double xi = ni.x, yi = ni.y, zi = ni.z;
-        const int grp = fin.bc;
-        if (grp >= 0) {
-            for (;;) {
-                const int gw = __builtin_amdgcn_readfirstlane(grp);
-                if (gw != grp) continue;
-                const DevBC& B = s.bcs[gw];
-                const bool met_it = ramp && gw == ramp->group && sp == ramp->sp;
-                const double r = met_it ? ramp->value : ramp_value(s, B, sp, dt);
-#pragma unroll
-                for (int c = 0; c < 3; ++c)
-                    if (B.mask & (1 << c))
-                        v[c] = B.v_max[c] * r + (B.grad[3 * c] * xi + B.grad[3 * c + 1] * yi +
-                                                 B.grad[3 * c + 2] * zi);
-                break;
-            }
-        }
-        if (Di >= 1.0) v[0] = v[1] = v[2] = 0.0;
-        double un[3] = {ni.ux + dt * v[0], ni.uy + dt * v[1], ni.uz + dt * v[2]};
-        if (known ? met->has_wall : P.has_wall) {
-            const double xw[3] = {xi + un[0], yi + un[1], zi + un[2]};
-            const double dn = xw[0] * P.wall_n[0] + xw[1] * P.wall_n[1] + xw[2] * P.wall_n[2] - P.wall_d;
-            if (dn < 0.0) {
-                un[0] = (xw[0] - dn * P.wall_n[0]) - xi;
-                un[1] = (xw[1] - dn * P.wall_n[1]) - yi;
-                un[2] = (xw[2] - dn * P.wall_n[2]) - zi;
-                const double vn = v[0] * P.wall_n[0] + v[1] * P.wall_n[1] + v[2] * P.wall_n[2];
-                if (vn < 0.0) {
-                    v[0] -= vn * P.wall_n[0];
-                    v[1] -= vn * P.wall_n[1];
-                    v[2] -= vn * P.wall_n[2];
+        finish_particle<R, kTwo>(
+            s, i, par, sp, P, finish_spec<kVarH>(P), ni, A, fin, sub,
+            [&](double dt, double xi, double yi, double zi, double (&v)[3]) {
+                for (;;) {
+                    const int gw = __builtin_amdgcn_readfirstlane(fin.bc);
+                    if (gw != fin.bc) continue;
+                    const DevBC& B = s.bcs[gw];
+                    const bool known = ramp && gw == ramp->group && sp == ramp->sp;
+                    prescribe(B, known ? ramp->value : ramp_value(s, B, sp, dt), xi, yi, zi, v);
+                    return;
                 }
-            }
-        }
-        const double w = Vi * (1.0 - Di);
-        const bool keep = (s.flags & kFlagStoreForce) || grp >= 0;
-        if constexpr (kTwo) {
-            reinterpret_cast<double2*>(s.VW)[2 * i + sub] = sub ? double2{v[2], w} : double2{v[0], v[1]};
-            reinterpret_cast<double2*>(s.U[par ^ 1])[2 * i + sub] =
-                sub ? double2{un[2], 0.0} : double2{un[0], un[1]};
-            if (keep) {
-                s.force[sub * np + i] = Vi * (sub ? fv1 : fv0);
-                if (!sub) s.force[2 * np + i] = Vi * fv2;
-            }
-        } else {
-            s.VW[i] = D4{v[0], v[1], v[2], w};
-            s.U[par ^ 1][i] = D4{un[0], un[1], un[2], 0.0};
-            if (keep) {
-                s.force[i] = Vi * fv0; s.force[np + i] = Vi * fv1; s.force[2 * np + i] = Vi * fv2;
-            }
-        }
+            });
         return;
     }
 }
@@ -1516,7 +1499,11 @@ __device__ __forceinline__ void force_finish(const DevState& s, int64_t i, int p
 // Then v += dt f / m, prescribed velocities at t^{n+1/2}, D = 1 at rest,
 // u^{n+1} = u^n + dt v (into the other displacement buffer), rigid wall, and
 // the record (v, V0 (1 - D)) the deformation pass gathers.  This variant
-// gathers neighbours straight from global memory.
+// gathers neighbours straight from global memory.  It is chosen for problems of
+// a few waves, which a chain of latencies bounds: what the finish needs of the
+// specimen is loaded per lane ahead of the pair sums, and of its group where it
+// has one (by wave, as the staged forms do, both ahead of the sums: 6k particles,
+// four lanes, a step of 17.5 us FP64, 16.5 mixed; so 17.1 and 16.1).
 template <typename R, int S, bool kVarH = false>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(S < 2 ? S : 2, 8)))
 k_pass_b(DevState s, int par) {
@@ -1536,25 +1523,27 @@ k_pass_b(DevState s, int par) {
     const R inv_h = R(P.inv_h);
     const bool live = in && !frozen(s, sp);
     const int cnt = live ? s.nnb[i] : 0;
+    const FinishSpec fsp = finish_spec<kVarH>(P);
     const FinishIn fin = finish_in(s, ii, XV[ii].w);
     const int32_t* __restrict__ cp = s.col + s.slice_ptr[ii / kSlice] + (ii % kSlice);
     const auto idx = [&](int k) { return (int)cp[(int64_t)k * kSlice]; };
-    Ramp ramp;
-    Met met;
     const ForceAcc<R> A = pair_sums<R, S, kVarH>(
         ni, cnt, sub, inv_h, idx,
         [&](int j) {
             LRecB<R> r = make_recb<R>(XV[j], GQ[j], GH[j], Uc[j]);
             if constexpr (kVarH) r.hs = s.hs[j];
             return r;
-        },
-        [&] { met = meet<kVarH>(s, sp, fin.bc, ramp); });
+        });
     // the particle's own Q is needed only now: reread it (the compiler barrier
     // keeps the load here) rather than keep it in registers through the loop
     asm volatile("" ::: "memory");
     if (live && sub == 0)
-        force_finish<R, kVarH>(s, i, par, sp, make_recb<R>(XV[i], GQ[i], GH[i], Uc[i]), A, fin,
-                               &ramp, 0, &met);
+        finish_particle<R, false>(s, i, par, sp, P, fsp, make_recb<R>(XV[i], GQ[i], GH[i], Uc[i]), A,
+                                  fin, 0,
+                                  [&](double dt, double xi, double yi, double zi, double (&v)[3]) {
+                                      const DevBC& B = s.bcs[fin.bc];
+                                      prescribe(B, ramp_value(s, B, sp, dt), xi, yi, zi, v);
+                                  });
 }
 
 // 16 bytes per lane from global memory straight into LDS: lane l of the wave
