@@ -233,7 +233,6 @@ void wire_state(tlsph_ctx* c) {
     s.nnb = at<int32_t>(c, L.nnb);
     s.slice_ptr = at<int64_t>(c, L.slice_ptr);
     s.col = at<int32_t>(c, L.col);
-    s.col_cap = (int64_t)L.k_cap * L.np;
     s.lcol = at<uint16_t>(c, L.lcol);
     s.halo = at<int32_t>(c, L.halo);
     s.halo_cnt = at<int32_t>(c, L.halo_cnt);

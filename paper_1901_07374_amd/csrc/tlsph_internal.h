@@ -137,7 +137,6 @@ struct DevState {
     const int32_t* nnb;      // neighbour count
     const int64_t* slice_ptr;
     const int32_t* col;
-    int64_t col_cap;         // entries of col (k_cap * np)
     const double* Linv;      // SoA [9][np]
     const float* Linv32;     // mixed form copy
     const DevSpec* specs;
@@ -187,7 +186,7 @@ struct DevState {
     int32_t contact;          // 1 if a specimen has penalty contact
     int32_t tile;             // particles per tile of the staged force pass (<= kTile)
     int32_t form_b;           // form of the staged force pass (kForm*), over grid_b workgroups
-    int32_t grid_b, pad4_;
+    int32_t grid_b;
     // The staged deformation pass's tiles: the force pass's (the same
     // arrays), or a size of their own (arrays of their own).
     int32_t staged_lds_a;     // 1 when the tile records of the deformation pass fit LDS
@@ -195,7 +194,6 @@ struct DevState {
     int32_t tile_a;           // its particles per tile
     int32_t halo_cap_a;
     int32_t lds_slots_a;      // slots of one tile's image
-    int32_t pad3_;
     const int32_t* halo_a;
     const int32_t* halo_cnt_a;
     const uint16_t* lcol_a;
@@ -210,6 +208,10 @@ struct DevState {
     int32_t* tile_list_a;
     int32_t* run_count;
 };
+// The record travels with every launch: one of 504 bytes (768 of arguments with
+// what the runtime adds) costs each kernel 0.2 us more than one of 488 (752).  A
+// step of 6k particles takes 16.9 us so, 17.15 with the larger one.
+static_assert(sizeof(DevState) <= 488, "the kernels' arguments stay below 768 bytes");
 
 enum : uint32_t { kFlagStoreForce = 1u, kFlagGraphs = 2u, kFlagCheckFinite = 4u,
                   kFlagNoStaging = 8u };

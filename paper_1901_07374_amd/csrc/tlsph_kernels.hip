@@ -569,7 +569,6 @@ __global__ void k_shape(DevState s, double* __restrict__ Linv, float* __restrict
         }
         return;
     }
-    if (s.slice_ptr[np / kSlice] > s.col_cap) return;  // list did not fit: never read col
     const DevSpec& P = s.specs[s.spec[p]];
     const D4 xp = s.XV[p];
     double L[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
