@@ -2657,8 +2657,14 @@ __device__ __forceinline__ void pass_a_update(const DevState& s, int64_t i, int 
 #pragma unroll
     for (int k = 0; k < 9; ++k) ho.h[k] = o.H[k];
     go.omd = R(1.0 - o.D);
-    // V0 (1 - D) for the force pass: kept with H, and unless D changed as it was
-    ho.vw = o.D != Di ? R(s.XV[is].w) * go.omd : vw;
+    // V0 (1 - D) for the force pass, kept with H: as it was unless D changed.  FP64:
+    // formed anew from V0 (read again, as L^-1 is: cached), since the value held
+    // through the update costs spills (1M particles 153 us, so 149; mixed 4.1M,
+    // which has registers for it, 512 and 516)
+    if constexpr (std::is_same<R, double>::value)
+        ho.vw = s.XV[is].w * go.omd;
+    else
+        ho.vw = o.D != Di ? R(s.XV[is].w) * go.omd : vw;
     GQ[is] = go;
     GH[is] = ho;
     // The plastic strain and its accumulators change only where the particle
