@@ -21,6 +21,7 @@ using namespace tlsph;
 namespace {
 
 constexpr size_t kAlign = 256;
+constexpr size_t kLdsGranule = 1280;   // LDS is handed out in units of this many bytes
 
 size_t align_up(size_t x) { return (x + kAlign - 1) & ~(kAlign - 1); }
 
@@ -453,20 +454,26 @@ tlsph_status build_tile_lists(tlsph_ctx* c, int T, size_t halo, size_t halo_cnt,
 }
 
 // The form of the staged force pass at the current tiles with `sub` lanes per
-// particle; every form gives the same bits.  Measured on whole passes:
-// - FP64, two sweeps where their smaller image lets more workgroups share a CU
-//   and the tiles need the room (395k particles, tiles of 97, three instead of
-//   two: 99.8 us, 118 in one sweep); else one sweep: one barrier instead of
-//   three (25k particles FP64, every tile resident at once: 12.6 us, 13.3 in two
-//   sweeps).
+// particle; every form gives the same bits.  Measured on force passes of bars,
+// plates, colliding and Taylor bars of 60k to 1M particles, tiles of 64 to 256:
+// - One sweep: one barrier instead of three (25k particles FP64, every tile
+//   resident at once: 12.6 us, 13.3 in two sweeps).
+// - FP64, two sweeps where the tiles need the room and their smaller image lets
+//   more workgroups share a CU, if that pays for the barriers: two instead of one
+//   do, up to 128 particles (200k, tiles of 128: 41.7 and 58.8 us); tiles of a
+//   wave or little more do (1 lane, 64: 66.0 and 75.9; 4 lanes, 64: 40.5 and
+//   43.3); with two lanes three instead of two do with contact, whose finish is
+//   long (395k, 97: 98 and 119), or on four waves, the last nearly empty (97 to
+//   100 particles: 39.2 and 41.2), not on three (200k, 72 to 91: 44 to 51 and 39
+//   to 44).  More than two waves with one lane, or four with four, leave no
+//   registers for a third workgroup (66 to 98: 4 to 22 % slower).
 // - In their place, pipelined over as many workgroups as fit (two lanes, one
 //   support for all, every particle's pairs within its registers, the image in
-//   LDS) where that is as many to a CU as the other form has (FP64: or 160
-//   particles to a CU), and each takes three tiles or more.  FP64, 4.1M particles: tiles of 256, one to a CU either
-//   way, 631 us; tiles of 128, one against two, 851 and 757; 200k, tiles of 160,
-//   one against two, 45.5 and 53.7.  Mixed: plate 2M,
-//   tiles of 128, two and two, 255 and 309; tiles of 192, one and two, 308 and
-//   295; plate 0.5M, tiles of 128, two and three, 63.4 and 61.5.
+//   LDS) where they have more than two and a half tiles each on average.  FP64
+//   from tiles of over 128 particles, one to a CU (1M, 256: 158 us, 222 in one
+//   sweep; 144: 212 and 293; 128: 202, two sweeps 182; 80, two to a CU: 236 and
+//   one sweep 197).  Mixed where as many share a CU as in one sweep (1M, tiles of
+//   128, two and two: 117 and 139; of 192, one and two: 147 and 139).
 tlsph_status set_form_b(tlsph_ctx* c, int sub) {
     const Layout& L = c->L;
     const bool var_h = c->st.var_h != 0;
@@ -478,7 +485,11 @@ tlsph_status set_form_b(tlsph_ctx* c, int sub) {
     c->st.grid_b = (int32_t)tiles;
     c->st.form_b = kFormOne;
     c->lds_b = one;
-    if (!L.mixed && lds / two > lds / one && tiles > (int64_t)(lds / one) * c->n_cu) {
+    const int T = c->st.tile;
+    const auto per = [&](size_t bytes) { return lds / ((bytes + kLdsGranule - 1) / kLdsGranule * kLdsGranule); };
+    const size_t w1 = per(one), w2 = per(two);
+    const bool paid = T <= 68 || (T <= 128 && (w1 == 1 || (sub == 2 && (T > 96 || c->st.contact))));
+    if (!L.mixed && w2 > w1 && paid && tiles > (int64_t)w1 * c->n_cu) {
         c->st.form_b = kFormSweeps;
         c->lds_b = two;
     }
@@ -487,8 +498,7 @@ tlsph_status set_form_b(tlsph_ctx* c, int sub) {
         HIPCHK(c, prepare_staged(pipe));
         HIPCHK(c, staged_blocks_per_cu(L.mixed, c->st.tile * sub, pipe, &per_cu));
         const int64_t room = (int64_t)c->n_cu * per_cu;
-        const bool many = per_cu >= (int)(lds / c->lds_b) ||
-                          (!L.mixed && per_cu * c->st.tile >= 160);
+        const bool many = L.mixed ? per_cu >= (int)w1 : T > 128 && per_cu >= 1;
         if (many && 2 * tiles > 5 * room) {
             c->st.form_b = kFormPipe;
             c->lds_b = pipe;

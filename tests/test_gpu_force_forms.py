@@ -106,3 +106,12 @@ def test_groups_of_several_specimens_in_a_wave(tl, precision, tile):
     assert inf["lds_bytes"] % BYTES["pipe"][precision == "mixed"] == 0
     for k in outs[0]:
         assert np.array_equal(outs[0][k], outs[1][k]), k
+
+
+@pytest.mark.parametrize("tile,form", [(80, "one"), (120, "two"), (128, "two"), (129, "pipe"),
+                                       (144, "pipe")])
+def test_form_at_the_rules_lines(tl, tile, form):
+    """Two lanes, FP64: two workgroups of 80 share a CU in one sweep and in the
+    pipelined form, whose image does not pay at that size; up to 128 particles two
+    share it in two sweeps alone; above, one does in any form."""
+    test_forms_are_bitwise_the_unstaged_pass(tl, "bar", "fp64", 2, tile, form)
