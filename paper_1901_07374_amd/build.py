@@ -46,7 +46,7 @@ def source_hash() -> str:
     sources are recognised as stale."""
     import hashlib
     h = hashlib.sha1()
-    for f in ("tlsph_kernels.hip", "tlsph_math.h", "tlsph_internal.h"):
+    for f in ("tlsph_kernels.hip", "tlsph_passes.h", "tlsph_math.h", "tlsph_internal.h"):
         with open(os.path.join(HERE, "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
