@@ -862,10 +862,8 @@ static hipError_t launch_b(const DevState& s, int parity, int block, bool mixed,
             }
         } else if (s.form_b == kFormPipe) {
             if (S != 2 || s.var_h) return hipErrorInvalidValue;
-            if (mixed)
-                k_pass_b_staged<float, 2><<<grid, threads, lds_bytes, st>>>(s, parity);
-            else
-                k_pass_b_staged<double, 2><<<grid, threads, lds_bytes, st>>>(s, parity);
+            if (!mixed) return launch_pipe_fp64(s, parity, st, lds_bytes);
+            k_pass_b_staged<float, 2><<<grid, threads, lds_bytes, st>>>(s, parity);
         } else {
             if (mixed) return hipErrorInvalidValue;
             if (s.var_h)
@@ -920,8 +918,7 @@ int staged_pipe_neighbours() { return kSub * kPipeGroups; }
 // Workgroups of the pipelined force pass (threads and LDS bytes each) that
 // share a CU.
 hipError_t staged_blocks_per_cu(bool mixed, int threads, size_t lds_bytes, int* out) {
-    const void* f = mixed ? reinterpret_cast<const void*>(&k_pass_b_staged<float, 2>)
-                          : reinterpret_cast<const void*>(&k_pass_b_staged<double, 2>);
+    const void* f = mixed ? reinterpret_cast<const void*>(&k_pass_b_staged<float, 2>) : pipe_fp64();
     return hipOccupancyMaxActiveBlocksPerMultiprocessor(out, f, threads, lds_bytes);
 }
 
@@ -932,7 +929,7 @@ hipError_t prepare_staged(size_t lds_bytes_b) {
     const void* const fns[] = {
         reinterpret_cast<const void*>(&k_pass_b_wide),
         reinterpret_cast<const void*>(&k_pass_b_staged<double, 1>),
-        reinterpret_cast<const void*>(&k_pass_b_staged<double, 2>),
+        pipe_fp64(),
         reinterpret_cast<const void*>(&k_pass_b_staged<float, 2>),
         reinterpret_cast<const void*>(&k_pass_b_staged<double, 4>),
         reinterpret_cast<const void*>(&k_pass_b_staged<double, 1, true>),
@@ -959,49 +956,43 @@ hipError_t prepare_staged(size_t lds_bytes_b) {
 }
 
 template <int DM, bool kFlow, bool kVarH = false>
-static void launch_a(const DevState& s, int parity, unsigned grid, int block, bool mixed,
-                     hipStream_t st) {
-    if (block == 0) {   // staged over its tiles, a_group of them per workgroup
-        const int64_t tiles = (s.n + s.tile_a - 1) / s.tile_a;
-        const unsigned groups = (unsigned)((tiles + s.a_group - 1) / s.a_group);
-        const int threads = s.tile_a * s.a_group;
-        const size_t lds = (size_t)s.a_group * s.lds_slots_a * staged_a_record_bytes(kVarH);
-        if (mixed)
-            k_pass_a_staged<float, DM, kFlow, kVarH><<<groups, threads, lds, st>>>(s, parity);
+static void launch_a(const DevState& s, int parity, int block, bool mixed, hipStream_t st) {
+    if (mixed) {
+        if constexpr (registers_full<float, DM, kFlow>())
+            launch_update_full(s, parity, block, DM, true, st);
         else
-            k_pass_a_staged<double, DM, kFlow, kVarH><<<groups, threads, lds, st>>>(s, parity);
-        return;
+            launch_update<float, DM, kFlow, kVarH>(s, parity, block, st);
+    } else {
+        if constexpr (registers_full<double, DM, kFlow>())
+            launch_update_full(s, parity, block, DM, false, st);
+        else
+            launch_update<double, DM, kFlow, kVarH>(s, parity, block, st);
     }
-    if (mixed)
-        k_pass_a<float, DM, kFlow, kVarH><<<grid, block, 0, st>>>(s, parity);
-    else
-        k_pass_a<double, DM, kFlow, kVarH><<<grid, block, 0, st>>>(s, parity);
 }
 
 hipError_t launch_pass_a(const DevState& s, int parity, int block, bool mixed, hipStream_t st) {
     if (block == 0 && (!s.staged_lds_a || s.a_group < 1 || s.a_group > 2 ||
                        s.tile_a * s.a_group > 256))
         return hipErrorInvalidValue;
-    const unsigned grid = block > 0 ? (unsigned)((s.n + block - 1) / block) : 0u;
     if (s.var_h) {   // graded spacing: the general variant with per-pair supports
-        launch_a<-1, true, true>(s, parity, grid, block, mixed, st);
+        launch_a<-1, true, true>(s, parity, block, mixed, st);
         return hipGetLastError();
     }
     if (s.flow_general) {
         switch (s.model) {
-            case 0: launch_a<0, true>(s, parity, grid, block, mixed, st); break;
-            case 1: launch_a<1, true>(s, parity, grid, block, mixed, st); break;
-            case 2: launch_a<2, true>(s, parity, grid, block, mixed, st); break;
-            case 3: launch_a<3, true>(s, parity, grid, block, mixed, st); break;
-            default: launch_a<-1, true>(s, parity, grid, block, mixed, st); break;
+            case 0: launch_a<0, true>(s, parity, block, mixed, st); break;
+            case 1: launch_a<1, true>(s, parity, block, mixed, st); break;
+            case 2: launch_a<2, true>(s, parity, block, mixed, st); break;
+            case 3: launch_a<3, true>(s, parity, block, mixed, st); break;
+            default: launch_a<-1, true>(s, parity, block, mixed, st); break;
         }
     } else {
         switch (s.model) {
-            case 0: launch_a<0, false>(s, parity, grid, block, mixed, st); break;
-            case 1: launch_a<1, false>(s, parity, grid, block, mixed, st); break;
-            case 2: launch_a<2, false>(s, parity, grid, block, mixed, st); break;
-            case 3: launch_a<3, false>(s, parity, grid, block, mixed, st); break;
-            default: launch_a<-1, false>(s, parity, grid, block, mixed, st); break;
+            case 0: launch_a<0, false>(s, parity, block, mixed, st); break;
+            case 1: launch_a<1, false>(s, parity, block, mixed, st); break;
+            case 2: launch_a<2, false>(s, parity, block, mixed, st); break;
+            case 3: launch_a<3, false>(s, parity, block, mixed, st); break;
+            default: launch_a<-1, false>(s, parity, block, mixed, st); break;
         }
     }
     return hipGetLastError();

@@ -2050,4 +2050,31 @@ k_pass_a_staged(DevState s, int /* displacement buffer: unused here */) {
     }
 }
 
+// Launch of one deformation pass: `block` threads per workgroup, or 0 for the
+// pass staged over its tiles, a_group of them per workgroup.
+template <typename R, int DM, bool kFlow, bool kVarH = false>
+static void launch_update(const DevState& s, int parity, int block, hipStream_t st) {
+    if (block == 0) {
+        const int64_t tiles = (s.n + s.tile_a - 1) / s.tile_a;
+        const unsigned groups = (unsigned)((tiles + s.a_group - 1) / s.a_group);
+        const size_t lds = (size_t)s.a_group * s.lds_slots_a * staged_a_record_bytes(kVarH);
+        k_pass_a_staged<R, DM, kFlow, kVarH><<<groups, s.tile_a * s.a_group, lds, st>>>(s, parity);
+    } else {
+        const unsigned grid = (unsigned)((s.n + block - 1) / block);
+        k_pass_a<R, DM, kFlow, kVarH><<<grid, block, 0, st>>>(s, parity);
+    }
+}
+
+// Deformation passes whose registers are full (at three waves per SIMD, 168):
+// FP64 with the GTN model's loops, mixed with every flow law; compiled, as the
+// pipelined force pass FP64 is (252 registers), in a source of their own.
+template <typename R, int DM, bool kFlow>
+constexpr bool registers_full() {
+    return sizeof(R) == 8 ? DM == 3 : kFlow;
+}
+hipError_t launch_pipe_fp64(const DevState& s, int parity, hipStream_t st, size_t lds_bytes);
+const void* pipe_fp64();
+void launch_update_full(const DevState& s, int parity, int block, int model, bool mixed,
+                        hipStream_t st);
+
 }  // namespace tlsph
