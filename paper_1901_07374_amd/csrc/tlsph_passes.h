@@ -1491,6 +1491,15 @@ k_pass_b_one(DevState s, int par) {
     const int cnt = in ? s.nnb[i] : 0;
     const int sp = s.spec[ii];
     const Slots<S> slots = load_slots<S>(s.pslot, ii, sub);
+    // (neighbours past the packed slots, which graded spacing often has: the first
+    // of them too ahead of the staging)
+    const uint16_t* __restrict__ lp = s.lcol + s.slice_ptr[ii / kSlice] + (ii % kSlice);
+    int q[NP];
+    const auto tail = [&](int k) { return (int)lp[(int64_t)(k < cnt ? k : 0) * kSlice]; };
+    if constexpr (kVarH) {
+#pragma unroll
+        for (int t = 0; t < NP; ++t) q[t] = tail(G * kSub + sub + S * t);
+    }
     const R inv_h = R(s.specs[sp].inv_h);
     constexpr bool kEarly = one_sweep_finish_early<R, S>();
     FinishIn fin_early;
@@ -1544,20 +1553,16 @@ k_pass_b_one(DevState s, int par) {
                                          g * kSub + sub + S * t < cnt);
             }
         if (G * kSub < cnt) {   // neighbours past the packed slots, loaded one group ahead
-            const uint16_t* __restrict__ lp = s.lcol + s.slice_ptr[ii / kSlice] + (ii % kSlice);
-            int q[NP];
+            if constexpr (!kVarH) {
 #pragma unroll
-            for (int t = 0; t < NP; ++t) {
-                const int k = G * kSub + sub + S * t;
-                q[t] = lp[(int64_t)(k < cnt ? k : 0) * kSlice];
+                for (int t = 0; t < NP; ++t) q[t] = tail(G * kSub + sub + S * t);
             }
             for (int k0 = G * kSub; k0 < cnt; k0 += kSub) {
                 int cur[NP];
 #pragma unroll
                 for (int t = 0; t < NP; ++t) {
                     cur[t] = q[t];
-                    const int kn = k0 + kSub + sub + S * t;
-                    q[t] = lp[(int64_t)(kn < cnt ? kn : 0) * kSlice];
+                    q[t] = tail(k0 + kSub + sub + S * t);
                 }
 #pragma unroll
                 for (int t = 0; t < NP; ++t)
