@@ -462,11 +462,12 @@ tlsph_status build_tile_lists(tlsph_ctx* c, int T, size_t halo, size_t halo_cnt,
 //   more workgroups share a CU, if that pays for the barriers: two instead of one
 //   do, up to 128 particles (200k, tiles of 128: 41.7 and 58.8 us); tiles of a
 //   wave or little more do (1 lane, 64: 66.0 and 75.9; 4 lanes, 64: 40.5 and
-//   43.3); with two lanes three instead of two do with contact, whose finish is
-//   long (395k, 97: 98 and 119), or on four waves, the last nearly empty (97 to
-//   100 particles: 39.2 and 41.2), not on three (200k, 72 to 91: 44 to 51 and 39
-//   to 44).  More than two waves with one lane, or four with four, leave no
-//   registers for a third workgroup (66 to 98: 4 to 22 % slower).
+//   43.3), but not with graded spacing and two lanes (80k, 64: 39.2 and 34.5);
+//   with two lanes three instead of two do with contact, whose finish is long
+//   (395k, 97: 98 and 119), or on four waves, the last nearly empty (97 to 100
+//   particles: 39.2 and 41.2), not on three (200k, 72 to 91: 44 to 51 and 39 to
+//   44).  More than one wave with one lane, or four with four, leave no registers
+//   for a third workgroup (66 to 98: 4 to 22 % slower).
 // - In their place, pipelined over as many workgroups as fit (two lanes, one
 //   support for all, every particle's pairs within its registers, the image in
 //   LDS) where they have more than two and a half tiles each on average.  FP64
@@ -488,7 +489,8 @@ tlsph_status set_form_b(tlsph_ctx* c, int sub) {
     const int T = c->st.tile;
     const auto per = [&](size_t bytes) { return lds / ((bytes + kLdsGranule - 1) / kLdsGranule * kLdsGranule); };
     const size_t w1 = per(one), w2 = per(two);
-    const bool paid = T <= 68 || (T <= 128 && (w1 == 1 || (sub == 2 && (T > 96 || c->st.contact))));
+    const bool paid = (T <= 68 && (sub != 2 || !var_h)) ||
+                      (T <= 128 && (w1 == 1 || (sub == 2 && (T > 96 || c->st.contact))));
     if (!L.mixed && w2 > w1 && paid && tiles > (int64_t)w1 * c->n_cu) {
         c->st.form_b = kFormSweeps;
         c->lds_b = two;

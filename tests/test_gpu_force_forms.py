@@ -115,3 +115,58 @@ def test_form_at_the_rules_lines(tl, tile, form):
     pipelined form, whose image does not pay at that size; up to 128 particles two
     share it in two sweeps alone; above, one does in any form."""
     test_forms_are_bitwise_the_unstaged_pass(tl, "bar", "fp64", 2, tile, form)
+
+
+def mild(scale):
+    """Two zones of spacings 1 and 1.1: a graded bar whose tiles stay small."""
+    return I.graded_notched_bar(R=2e-3, L=10e-3, rho=1e-3, bounds=(2e-3,),
+                                spacings=(scale * 0.2e-3, scale * 0.22e-3))
+
+
+@pytest.mark.parametrize("lanes,tile,form", [(1, 64, "two"), (1, 128, "two"), (2, 128, "two"),
+                                             (2, 112, "two"), (4, 64, "two"), (4, 112, "two"),
+                                             (2, 64, "one"), (4, 80, "one")])
+def test_graded_forms_are_bitwise_the_unstaged_pass(tl, lanes, tile, form):
+    """Each pair's own support: its radii's plane in the image, the constant
+    factor in what the first sweep keeps, more neighbours than the packed slots."""
+    p = mild(0.521)
+    st = I.random_state(p, seed=17, v_scale=1.0, u_scale=1e-7)
+    outs = []
+    for shape in ((False, 4, 256, 256, 0), (True, lanes, 256, 256, tile)):
+        g = tl.Sim(p, flags=tl.STORE_FORCE, k_cap=64)
+        g.set_launch_shape(*shape)
+        g.set_state(st)
+        g.step(3)
+        outs.append({k: g.get(k) for k in KEYS})
+        inf = g.info()
+    print(lanes, tile, p.n, inf, flush=True)
+    per_slot = BYTES[form][0] + 8
+    assert inf["lds_bytes"] % per_slot == 0 and inf["lds_bytes"] > tile * per_slot
+    for k in KEYS:
+        assert np.array_equal(outs[0][k], outs[1][k]), k
+
+
+@pytest.mark.parametrize("problem,precision,tile", [
+    ("bar", "fp64", 163), ("bar", "fp64", 195), ("bar_large", "mixed", 128),
+    ("bar_large", "mixed", 227), ("contact_av", "fp64", 192), ("stopped", "fp64", 193)])
+def test_pipelined_pass_without_stored_forces(tl, problem, precision, tile):
+    """The finish's two stores are then the wave's last, which its wait for the
+    next tile's copies counts on exactly (with forces stored it waits for more)."""
+    p = PROBLEMS[problem]()
+    st = I.random_state(p, seed=19, v_scale=1.0, u_scale=1e-7)
+    outs = []
+    for shape in ((False, 4, 256, 256, 0), (True, 2, 256, 256, tile)):
+        g = tl.Sim(p, precision=tl.FP64 if precision == "fp64" else tl.MIXED, k_cap=32)
+        g.set_launch_shape(*shape)
+        g.set_state(st)
+        if problem == "stopped":
+            g.set_run_control([{"step_cap": 2 if q == 1 else 0} for q in range(p.n_spec)])
+            g.run(6, check_every=1)
+        else:
+            g.step(6)
+        outs.append({k: g.get(k) for k in KEYS if k != "force"})
+        inf = g.info()
+    print(problem, precision, tile, p.n, inf, flush=True)
+    assert inf["lds_bytes"] % BYTES["pipe"][precision == "mixed"] == 0
+    for k in outs[0]:
+        assert np.array_equal(outs[0][k], outs[1][k]), k
