@@ -1930,9 +1930,30 @@ k_pass_a(DevState s, int /* displacement buffer: unused here */) {
 
 // Neighbour-index groups the staged deformation pass loads before its
 // staging.
-template <typename R, int DM, bool kFlow>
+template <typename R, bool kPacked>
 __host__ __device__ constexpr int staged_a_pre_groups() {
-    return sizeof(R) == 8 ? 6 : 3;
+    return sizeof(R) == 8 || kPacked ? kPackGroups : 3;
+}
+// The same from the packed slots (lists t, t + kSub, ... to groups of kGatherA).
+__device__ __forceinline__ PreIdxA<kPackGroups> packed_indices_a(const uint32_t* __restrict__ pslot,
+                                                                 int64_t i) {
+    static_assert(kGatherA == kSub && kPackGroups == 6 && kPackWords == 12, "three words a list");
+    uint32_t o[kPackWords];
+    const uint4* __restrict__ q = reinterpret_cast<const uint4*>(pslot + i * kPackWords);
+#pragma unroll
+    for (int w = 0; w < kPackWords / 4; ++w) {
+        const uint4 v = q[w];
+        o[4 * w] = v.x; o[4 * w + 1] = v.y; o[4 * w + 2] = v.z; o[4 * w + 3] = v.w;
+    }
+    PreIdxA<kPackGroups> p;
+#pragma unroll
+    for (int g = 0; g < kPackGroups; ++g)
+#pragma unroll
+        for (int t = 0; t < kGatherA; t += 2) {   // halves g % 2 of two lists' words
+            const uint32_t a = o[3 * t + g / 2], b = o[3 * (t + 1) + g / 2];
+            p.w[g][t >> 1] = (g & 1) ? (a >> 16) | (b & 0xffff0000u) : (a & 0xffffu) | (b << 16);
+        }
+    return p;
 }
 
 // The same pass over the force pass's tiles: the records of the tile and its
@@ -1941,9 +1962,11 @@ __host__ __device__ constexpr int staged_a_pre_groups() {
 // arithmetic in the same order as k_pass_a.
 // Graded spacing (kVarH): the support radius follows (64 bytes).
 constexpr int kLdsABytes = 56;
-template <typename R, int DM, bool kFlow, bool kVarH = false>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(pass_a_waves_min<R, DM, kFlow>(), 8)))
-k_pass_a_staged(DevState s, int /* displacement buffer: unused here */) {
+// kPacked: the first neighbours from the force pass's packed slots, not from the
+// sliced list, which is then hardly read: where both passes run over the same
+// tiles.
+template <typename R, int DM, bool kFlow, bool kVarH, bool kPacked>
+__device__ __forceinline__ void pass_a_staged(const DevState& s) {
     extern __shared__ __align__(16) unsigned char lds_a[];
     // G tiles per workgroup (two where a tile is not a whole number of waves),
     // each with an image of M slots of its own; thread tx of part `part`
@@ -1988,8 +2011,13 @@ k_pass_a_staged(DevState s, int /* displacement buffer: unused here */) {
     const int sp_lane = s.spec[ii];
     const uint16_t* __restrict__ lp = s.lcol_a + slice0 + (ii % kSlice);
     const auto idx = [&](int k) { return (int)lp[(int64_t)k * kSlice]; };
-    constexpr int kPre = staged_a_pre_groups<R, DM, kFlow>();
-    const PreIdxA<kPre> pre = pre_indices_a<kPre>(cnt, idx);
+    constexpr int kPre = staged_a_pre_groups<R, kPacked>();
+    const PreIdxA<kPre> pre = [&] {
+        if constexpr (kPacked)
+            return packed_indices_a(s.pslot, ii);
+        else
+            return pre_indices_a<kPre>(cnt, idx);
+    }();
     // whether the specimen runs and (FP64: the mixed form has no registers to
     // spare for them) what the neighbour sums need of it: also loaded before
     // the staging
@@ -2055,6 +2083,24 @@ k_pass_a_staged(DevState s, int /* displacement buffer: unused here */) {
     }
 }
 
+template <typename R, int DM, bool kFlow, bool kVarH = false>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(pass_a_waves_min<R, DM, kFlow>(), 8)))
+k_pass_a_staged(DevState s, int /* displacement buffer: unused here */) {
+    pass_a_staged<R, DM, kFlow, kVarH, false>(s);
+}
+
+// Mixed, with the packed slots: 36 bytes a particle less to read beside the force
+// pass's 48, for twelve registers more.  From about 450k particles on, where the
+// two passes' data no longer fit the caches that they share, that pays (Taylor bar
+// 599k, tiles of 128: 67.5 us, so 62.8; plate 567k, a step 142.1, so 137.7); below
+// it does not (bar 200k, 112: 27.0 and 27.3).
+constexpr int64_t kPackedFrom = 450000;
+template <int DM>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(pass_a_waves_min<float, DM, false>(), 8)))
+k_pass_a_packed(DevState s, int /* displacement buffer: unused here */) {
+    pass_a_staged<float, DM, false, false, true>(s);
+}
+
 // Launch of one deformation pass: `block` threads per workgroup, or 0 for the
 // pass staged over its tiles, a_group of them per workgroup.
 template <typename R, int DM, bool kFlow, bool kVarH = false>
@@ -2063,7 +2109,13 @@ static void launch_update(const DevState& s, int parity, int block, hipStream_t 
         const int64_t tiles = (s.n + s.tile_a - 1) / s.tile_a;
         const unsigned groups = (unsigned)((tiles + s.a_group - 1) / s.a_group);
         const size_t lds = (size_t)s.a_group * s.lds_slots_a * staged_a_record_bytes(kVarH);
-        k_pass_a_staged<R, DM, kFlow, kVarH><<<groups, s.tile_a * s.a_group, lds, st>>>(s, parity);
+        const int threads = s.tile_a * s.a_group;
+        if constexpr (sizeof(R) == 4 && !kFlow)
+            if (s.n >= kPackedFrom && s.lcol_a == s.lcol) {
+                k_pass_a_packed<DM><<<groups, threads, lds, st>>>(s, parity);
+                return;
+            }
+        k_pass_a_staged<R, DM, kFlow, kVarH><<<groups, threads, lds, st>>>(s, parity);
     } else {
         const unsigned grid = (unsigned)((s.n + block - 1) / block);
         k_pass_a<R, DM, kFlow, kVarH><<<grid, block, 0, st>>>(s, parity);
