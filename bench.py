@@ -76,10 +76,15 @@ def kernel_symbol(kernel: str, info: dict, mixed: bool, model: int, flow_general
     the kernels take per-pair supports (graded spacing: the general variant)."""
     r = "float" if mixed else "double"
     vh = "true" if var_h else "false"
+    name = info.get("kernels", {}).get(kernel)   # as the context reports it
     if kernel == "force_pass":
-        name = "k_pass_b_staged" if info["staged"] else "k_pass_b"
+        name = name or ("k_pass_b_staged" if info["staged"] else "k_pass_b")
+        if name == "k_pass_b_wide":
+            return name
         return f"{name}<{r}, {info['lanes_per_particle']}, {vh}>"
-    name = "k_pass_a_staged" if info["block_deformation"] <= 0 else "k_pass_a"
+    name = name or ("k_pass_a_staged" if info["block_deformation"] <= 0 else "k_pass_a")
+    if name == "k_pass_a_packed":
+        return f"{name}<{model}>"
     if var_h:
         model, flow_general = -1, True
     return f"{name}<{r}, {model}, {'true' if flow_general else 'false'}, {vh}>"
@@ -203,7 +208,7 @@ def run_form(prob, precision, steps, warmup, torch, T, flags=0, autotune=True, s
     kt = sim.kernel_times() if use_timing else None
     sim.enable_kernel_timing(0)
     log(f"  {steps} steps in {t1 - t0:.3f} s")
-    return dict(seconds=t1 - t0, kernel_times=kt, info=sim.info(), sim=sim,
+    return dict(seconds=t1 - t0, kernel_times=kt, info=dict(sim.info(), kernels=sim.kernel_names()), sim=sim,
                 sd=sd[:rec].cpu().numpy(), bd=bd[:rec].cpu().numpy())
 
 

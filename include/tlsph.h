@@ -314,6 +314,11 @@ tlsph_status tlsph_kernel_times(tlsph_ctx *ctx, double ms[2], int64_t launches[2
  * are read after the work already queued on the stream: synchronises it. */
 tlsph_status tlsph_info(tlsph_ctx *ctx, int64_t out[9], hipStream_t stream);
 
+/* Name of the kernel that a step of the context now launches for the force pass
+ * (pass 0) or the deformation pass (1), without its template arguments, as a
+ * profiler lists it; empty before a build or for another pass.  Host only. */
+const char *tlsph_kernel_name(const tlsph_ctx *ctx, int32_t pass);
+
 /* Pin the launch shape (host int32[5]): [0] 1 = LDS-staged force pass, 0 =
  * gathers from global memory; [1] lanes per particle of the force pass (1,
  * 2 or 4); [2] threads per block of the unstaged force pass (64, 128, 192 or

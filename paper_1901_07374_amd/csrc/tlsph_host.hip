@@ -1382,6 +1382,11 @@ tlsph_status tlsph_info(tlsph_ctx* c, int64_t out[9], hipStream_t stream) {
     return TLSPH_OK;
 }
 
+const char* tlsph_kernel_name(const tlsph_ctx* c, int32_t pass) {
+    if (!c || !c->built || pass < 0 || pass > 1) return "";
+    return pass == 0 ? pass_b_name(c->st, c->sub_b) : pass_a_name(c->st, c->block_a, c->L.mixed);
+}
+
 tlsph_status tlsph_set_launch_shape(tlsph_ctx* c, const int32_t shape[5], hipStream_t stream) {
     if (!c || !shape) return TLSPH_E_INVALID_ARG;
     if (!c->built) return fail(c, TLSPH_E_BAD_STATE, "launch shape before build");

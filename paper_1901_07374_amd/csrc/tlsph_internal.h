@@ -225,6 +225,9 @@ enum : int32_t { kErrNonFinite = 1, kErrNewton = 2, kErrContact = 4 };
 hipError_t launch_pass_b(const DevState& s, int parity, int block, int sub, bool mixed,
                          hipStream_t st, size_t lds_bytes = 0);
 hipError_t launch_pass_a(const DevState& s, int parity, int block, bool mixed, hipStream_t st);
+// The kernels that these launch.
+const char* pass_b_name(const DevState& s, int sub);
+const char* pass_a_name(const DevState& s, int block, bool mixed);
 
 // Slot of a cell hash: the contact search's (below), and the table of occupied
 // cells while the neighbour lists are built.

@@ -901,6 +901,18 @@ hipError_t launch_pass_b(const DevState& s, int parity, int block, int sub, bool
     }
 }
 
+const char* pass_b_name(const DevState& s, int sub) {
+    if (!s.staged) return "k_pass_b";
+    if (s.form_b == kFormOne) return "k_pass_b_one";
+    return s.form_b == kFormSweeps && sub == 2 && !s.var_h ? "k_pass_b_wide" : "k_pass_b_staged";
+}
+
+const char* pass_a_name(const DevState& s, int block, bool mixed) {
+    if (block != 0) return "k_pass_a";
+    return mixed && !s.flow_general && !s.var_h && update_packed(s) ? "k_pass_a_packed"
+                                                                    : "k_pass_a_staged";
+}
+
 int staged_tile_max(int sub) { return staged_block_max(sub) / sub; }
 
 size_t staged_one_bytes(bool mixed, bool var_h) {

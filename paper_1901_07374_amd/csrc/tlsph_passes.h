@@ -2095,6 +2095,9 @@ k_pass_a_staged(DevState s, int /* displacement buffer: unused here */) {
 // 599k, tiles of 128: 67.5 us, so 62.8; plate 567k, a step 142.1, so 137.7); below
 // it does not (bar 200k, 112: 27.0 and 27.3).
 constexpr int64_t kPackedFrom = 450000;
+static inline bool update_packed(const DevState& s) {
+    return s.n >= kPackedFrom && s.lcol_a == s.lcol;
+}
 template <int DM>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(pass_a_waves_min<float, DM, false>(), 8)))
 k_pass_a_packed(DevState s, int /* displacement buffer: unused here */) {
@@ -2111,7 +2114,7 @@ static void launch_update(const DevState& s, int parity, int block, hipStream_t 
         const size_t lds = (size_t)s.a_group * s.lds_slots_a * staged_a_record_bytes(kVarH);
         const int threads = s.tile_a * s.a_group;
         if constexpr (sizeof(R) == 4 && !kFlow)
-            if (s.n >= kPackedFrom && s.lcol_a == s.lcol) {
+            if (update_packed(s)) {
                 k_pass_a_packed<DM><<<groups, threads, lds, st>>>(s, parity);
                 return;
             }

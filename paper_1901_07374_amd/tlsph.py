@@ -109,6 +109,8 @@ def lib():
         L.tlsph_status_string.restype = C.c_char_p
         L.tlsph_last_error.argtypes = [_vp]
         L.tlsph_last_error.restype = C.c_char_p
+        L.tlsph_kernel_name.argtypes = [_vp, C.c_int32]
+        L.tlsph_kernel_name.restype = C.c_char_p
         for name in ("tlsph_workspace_bytes", "tlsph_create", "tlsph_build_neighbors",
                      "tlsph_step", "tlsph_get_state", "tlsph_set_state", "tlsph_neighbor_count",
                      "tlsph_get_neighbors", "tlsph_get_diagnostics",
@@ -325,6 +327,11 @@ class Sim:
         return dict(block_force=abs(out[0]), staged=out[0] < 0, block_deformation=out[1],
                     nnz=out[2], slots=out[3], n=out[4], flags=out[5],
                     lanes_per_particle=out[6], lds_bytes=out[7], tile=out[8])
+
+    def kernel_names(self) -> Dict[str, str]:
+        """Kernels that a step launches, without their template arguments."""
+        return {k: lib().tlsph_kernel_name(self.ctx, p).decode()
+                for p, k in enumerate(("force_pass", "deformation_pass"))}
 
     def set_contact(self, every: int = 1, skin: float = 0.0):
         """Rebuild the penalty-contact candidate lists every `every` steps

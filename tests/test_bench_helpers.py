@@ -52,6 +52,17 @@ def test_graded_and_general_symbols():
         "k_pass_a_staged<double, 1, true, false>"
 
 
+def test_symbols_of_the_reported_kernels():
+    def sym(kernel, name, mixed=False, lanes=2, **kw):
+        info = dict(STAGED, lanes_per_particle=lanes, kernels={kernel: name})
+        return bench.kernel_symbol(kernel, info, mixed, 2, **kw)
+    assert sym("force_pass", "k_pass_b_one", mixed=True, lanes=4) == "k_pass_b_one<float, 4, false>"
+    assert sym("force_pass", "k_pass_b_one", var_h=True) == "k_pass_b_one<double, 2, true>"
+    assert sym("force_pass", "k_pass_b_wide") == "k_pass_b_wide"
+    assert sym("force_pass", "k_pass_b_staged") == "k_pass_b_staged<double, 2, false>"
+    assert sym("deformation_pass", "k_pass_a_packed", mixed=True) == "k_pass_a_packed<2>"
+
+
 def test_algorithmic_bytes_of_the_headline_force_pass():
     # 308 bytes per particle and 4 per neighbour pair (200 216 particles,
     # 3 476 976 pairs)

@@ -170,3 +170,19 @@ def test_pipelined_pass_without_stored_forces(tl, problem, precision, tile):
     assert inf["lds_bytes"] % BYTES["pipe"][precision == "mixed"] == 0
     for k in outs[0]:
         assert np.array_equal(outs[0][k], outs[1][k]), k
+
+
+def test_kernel_names(tl):
+    """The context names the kernels it launches."""
+    g = tl.Sim(PROBLEMS["bar"]())
+    for shape, force, deform in (
+            ((False, 4, 128, 256, 0), "k_pass_b", "k_pass_a"),
+            ((True, 2, 256, 0, 80), "k_pass_b_one", "k_pass_a_staged"),
+            ((True, 2, 256, -64, 128), "k_pass_b_wide", "k_pass_a_staged"),
+            ((True, 4, 256, 64, 64), "k_pass_b_staged", "k_pass_a"),
+            ((True, 2, 256, 256, 192), "k_pass_b_staged", "k_pass_a")):
+        g.set_launch_shape(*shape)
+        assert g.kernel_names() == {"force_pass": force, "deformation_pass": deform}, shape
+    g = tl.Sim(PROBLEMS["bar_large"](), precision=tl.MIXED)
+    g.set_launch_shape(True, 2, 256, 0, 128)
+    assert g.kernel_names()["deformation_pass"] == "k_pass_a_staged"   # (below 450k particles)
