@@ -856,9 +856,9 @@ __host__ __device__ constexpr int staged_waves_min() {
 // unstaged kernel, so results are bitwise identical.  Two sweeps need 148
 // bytes of LDS per slot where one sweep's image takes 208, and fewer registers:
 // three tiles share a CU instead of two (395k particles with contact, tiles of
-// 97: 118 -> 100 us).  FP64 only: the mixed records save 12 bytes of 128.  The first sweep keeps each pair's V_j s / r in a
-// register for the second.  Graded spacing (kVarH): the slots' support radii are in
-// LDS too (one double per slot).
+// 97: 118 -> 100 us).  FP64 only: the mixed records save 12 bytes of 128.  The
+// first sweep keeps each pair's V_j s / r in a register for the second.  Graded
+// spacing (kVarH): the slots' support radii are in LDS too (one double per slot).
 template <int S, bool kVarH>
 __device__ __forceinline__ void pass_b_sweeps(const DevState& s, int par) {
     extern __shared__ __align__(16) unsigned char lds_raw[];
@@ -1112,10 +1112,10 @@ __device__ __forceinline__ void settle_here(R& a, R& b, R& c) {
 // the stress sums) runs, the next tile's positions, displacements, H and
 // neighbour slots, into what the first sweep is done with.  A wait is explicit,
 // once per sweep (vmcnt counts the finish's two stores too, issued last).
-// What bounds it: FP64 issue (366 us of VALU at 4.1M particles) and LDS (298 us,
-// over half of it bank conflicts of records read at random).  4.1M-particle
-// plate, FP64, tiles of 253: 717 -> 628 us; mixed 559 -> 500; Taylor bar 1M,
-// tiles of 217: 178 -> 172.
+// What bounds it: FP64 issue (1.89e8 VALU instructions at 4.1M particles, 307 us of
+// them on every SIMD) and LDS (bank conflicts of records read at random alone hold
+// it for 151 us).  4.1M-particle plate, FP64: one sweep, tiles of 96, 715 us, this,
+// tiles of 253, 617; mixed 558 and 490.
 template <typename R>
 __device__ __forceinline__ void pass_b_pipe(const DevState& s, int par) {
     extern __shared__ __align__(16) unsigned char lds_raw[];
@@ -1450,8 +1450,9 @@ __host__ __device__ constexpr bool one_sweep_finish_early() {
 // The staged force pass in one sweep over an image of whole records, staged
 // through registers, a workgroup per tile: a chain of few latencies, which is
 // what bounds it where tiles are few (25k particles FP64, tiles of 98: 12.3 us,
-// 12.8 with a load for each neighbour slot and the groups' records by lane).  Graded spacing (kVarH): the slots'
-// support radii follow the records in LDS (one double per slot).
+// 12.8 with a load for each neighbour slot and the groups' records by lane).
+// Graded spacing (kVarH): the slots' support radii follow the records in LDS (one
+// double per slot).
 template <typename R, int S, bool kVarH = false>
 __global__ void __launch_bounds__(staged_block_max(S))
 __attribute__((amdgpu_waves_per_eu(one_sweep_waves_min<R, S, kVarH>(), 8)))
